@@ -1,10 +1,12 @@
-// coarse.hip -- the bottom of the V-cycle in one workgroup.
+// coarse.hip -- the bottom of the V-cycle in one launch.
 //
 // Levels with at most kCoarseMax cells per side are too small to fill the
 // GPU, so one workgroup runs the whole rest of the V-cycle for them: from the
-// top level (n_top cells per side) down to the 2 x 2 grid and back up, every
-// level held in LDS (phi and f, no ghost layer: side rules are applied where a
-// neighbour is read).  The steps are those of the paper's V-cycle (Sec. 3.3):
+// top level (n_top cells per side) down to the 2 x 2 grid and back up.  From
+// 32 x 32 (any grid of 32^2 cells or more) that is one wavefront with every
+// level in registers (tail_body); a finest grid of 16^2 cells or fewer runs in
+// coarse_body, every level in LDS (phi and f, no ghost layer: side rules are
+// applied where a neighbour is read).  The steps are those of the paper's V-cycle (Sec. 3.3):
 // nu1 red-black Gauss-Seidel iterations, residual and four-cell restriction,
 // recursion, centred-slope prolongation without the xy term, nu2 iterations;
 // on the 2 x 2 grid nu_bottom relaxations, done in FP64 whatever T is.  Or an
@@ -18,10 +20,9 @@ namespace ccmg {
 
 namespace {
 
-// Workgroup size NT (a template parameter): 512 gives one thread per cell of a
-// colour on the 32 x 32 level (64, 128 and 256 measured slower).  With NT = 64
-// (one wavefront) no workgroup barrier would be needed -- a wave's LDS
-// operations complete in issue order, so ordering the compiler's code is
+// Workgroup size NT of coarse_body (a template parameter).  With NT = 64 (one
+// wavefront: a batch's small grids) no workgroup barrier is needed -- a wave's
+// LDS operations complete in issue order, so ordering the compiler's code is
 // enough between phases.
 constexpr int kCoarseThreads = 512;
 
@@ -184,42 +185,63 @@ __device__ void up_level(const CoarseArgs<T> &a, const Sides &sd, T *sP, const T
     relax<NTW>(sP + off[l], sF + off[l], lg, sd, T(a.cc[l]), T(a.invd[l]), a.nu2);
 }
 
-// Bottom: 2 x 2 grid, relaxation only, in FP64 registers of thread 0.
-// Cell q = 2y + x; its x-neighbour is q^1 and its y-neighbour q^2.  On a
-// 2 x 2 grid the periodic image of that neighbour is the same cell, and a
-// Dirichlet / Neumann ghost is -/+ the cell itself.
+// Bottom: 2 x 2 grid, relaxation only, in FP64 registers (f, p: the grid's
+// right-hand side and iterate).  Cell q = 2y + x; its x-neighbour is q^1 and
+// its y-neighbour q^2.  On a 2 x 2 grid the periodic image of that neighbour
+// is the same cell, and a Dirichlet / Neumann ghost is -/+ the cell itself.
+template <bool PX, bool PY>
+__device__ __forceinline__ void relax2_sides(double c, double invd, int iters, double xl, double xh, double yl,
+                                             double yh, const double (&f)[4], double (&p)[4]) {
+    double p0 = p[0], p1 = p[1], p2 = p[2], p3 = p[3];
+    // x-ghost of a cell at x = 0 is its west side (x-lo), at x = 1 its east side (x-hi)
+    auto upd = [&](double self, double ex, double ey, double fq, bool x0, bool y0) {
+        const double e = x0 ? ex : (PX ? ex : xh * self);
+        const double w = x0 ? (PX ? ex : xl * self) : ex;
+        const double nn = y0 ? ey : (PY ? ey : yh * self);
+        const double s = y0 ? (PY ? ey : yl * self) : ey;
+        return (fq + c * (((e + w) + nn) + s)) * invd;
+    };
+    // An iteration is a chain of ten dependent FP64 operations.  One that
+    // changes nothing is a fixed point: the remaining ones would return
+    // exactly these values.  That is looked at on every fourth only, off the chain.
+    for (int it = 0; it < iters;) {
+        bool same = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (it >= iters) break;
+            const double q0 = upd(p0, p1, p2, f[0], true, true);    // red (0,0)
+            const double q3 = upd(p3, p2, p1, f[3], false, false);  // red (1,1)
+            const double q1 = upd(p1, q0, q3, f[1], false, true);   // black (1,0)
+            const double q2 = upd(p2, q3, q0, f[2], true, false);   // black (0,1)
+            if (u == 3) same = q0 == p0 && q1 == p1 && q2 == p2 && q3 == p3;
+            p0 = q0, p1 = q1, p2 = q2, p3 = q3;
+            ++it;
+        }
+        if (same) break;
+    }
+    p[0] = p0, p[1] = p1, p[2] = p2, p[3] = p3;
+}
+__device__ __forceinline__ void relax2(double c, double invd, int iters, bool px, bool py, double xl, double xh,
+                                       double yl, double yh, const double (&f)[4], double (&p)[4]) {
+    if (px) {
+        if (py) relax2_sides<true, true>(c, invd, iters, xl, xh, yl, yh, f, p);
+        else relax2_sides<true, false>(c, invd, iters, xl, xh, yl, yh, f, p);
+    } else {
+        if (py) relax2_sides<false, true>(c, invd, iters, xl, xh, yl, yh, f, p);
+        else relax2_sides<false, false>(c, invd, iters, xl, xh, yl, yh, f, p);
+    }
+}
 template <typename T>
 __device__ void bottom(const CoarseArgs<T> &a, const Sides &sd, T *sP, const T *sF, const int *off, int L) {
     if (threadIdx.x != 0) return;
     const int l = L - 1;
-    const double c = a.cc[l], invd = a.invd[l];
-    double p0 = sP[off[l] + 0], p1 = sP[off[l] + 1], p2 = sP[off[l] + 2], p3 = sP[off[l] + 3];
-    const double f0 = sF[off[l] + 0], f1 = sF[off[l] + 1], f2 = sF[off[l] + 2], f3 = sF[off[l] + 3];
-    const double xl = sd.px ? 1.0 : (double)sd.sxl, xh = sd.px ? 1.0 : (double)sd.sxh;
-    const double yl = sd.py ? 1.0 : (double)sd.syl, yh = sd.py ? 1.0 : (double)sd.syh;
-    // x-ghost of a cell at x = 0 is its west side (x-lo), at x = 1 its east side (x-hi)
-    auto upd = [&](double self, double ex, double ey, double f, bool x0, bool y0) {
-        const double e = x0 ? ex : (sd.px ? ex : xh * self);
-        const double w = x0 ? (sd.px ? ex : xl * self) : ex;
-        const double nn = y0 ? ey : (sd.py ? ey : yh * self);
-        const double s = y0 ? (sd.py ? ey : yl * self) : ey;
-        return (f + c * (((e + w) + nn) + s)) * invd;
-    };
-    for (int it = 0; it < a.nu_bottom; ++it) {
-        const double q0 = upd(p0, p1, p2, f0, true, true);    // red (0,0)
-        const double q3 = upd(p3, p2, p1, f3, false, false);  // red (1,1)
-        const double q1 = upd(p1, q0, q3, f1, false, true);   // black (1,0)
-        const double q2 = upd(p2, q3, q0, f2, true, false);   // black (0,1)
-        // an iteration that changes nothing is a fixed point: the remaining
-        // iterations would return exactly these values
-        const bool same = q0 == p0 && q1 == p1 && q2 == p2 && q3 == p3;
-        p0 = q0, p1 = q1, p2 = q2, p3 = q3;
-        if (same) break;
+    double p[4], f[4];
+    for (int q = 0; q < 4; ++q) {
+        p[q] = sP[off[l] + q];
+        f[q] = sF[off[l] + q];
     }
-    sP[off[l] + 0] = T(p0);
-    sP[off[l] + 1] = T(p1);
-    sP[off[l] + 2] = T(p2);
-    sP[off[l] + 3] = T(p3);
+    relax2(a.cc[l], a.invd[l], a.nu_bottom, sd.px, sd.py, sd.sxl, sd.sxh, sd.syl, sd.syh, f, p);
+    for (int q = 0; q < 4; ++q) sP[off[l] + q] = T(p[q]);
 }
 
 // Exact bottom on level l (n = 1 << lg cells per side, m = n^2 unknowns), on
@@ -302,15 +324,495 @@ __device__ void coarse_body(const CoarseArgs<T> &a) {
     }
 }
 
+// ---- the tail of a 32 x 32 level on one wavefront ------------------------------
+// The whole of the tail is a serial chain: some 40 colour sweeps and
+// transfers, each waiting for the one before.  What bounds it is the latency
+// of a step, so every level lives in the registers of one wave: no barrier
+// between steps, no LDS addresses, neighbours by DPP moves along x (rows of 16
+// lanes, whose rotation is the periodic wrap) and one ds_bpermute per sweep
+// and direction between the four rows of lanes along y.
+//
+// Lane = 16 g + I, g = 0 .. 3, I = 0 .. 15:
+//   32 x 32: columns 2I, 2I + 1 of rows 8g .. 8g + 7 (one red and one black cell a row)
+//   16 x 16: column I of rows 4g .. 4g + 3, kept as two red and two black cells
+//    8 x 8:  the cell of column I / 2, row 2g + I % 2
+//    4 x 4:  the cell of column I / 4, row g (in all four lanes of a quad)
+//    2 x 2:  all four cells in every lane
+// so that restriction and prolongation move data within a quad of lanes only.
+// The arithmetic of a cell is coarse_body's, operation for operation: the same
+// bits (for singular problems, whose means are summed in another order, up to
+// rounding).
+// Per launch, some 2.5 us of it the launch itself, against coarse_body on 512
+// threads: FP64 all-Dirichlet (50 bottom iterations) 22.1 -> 9.9 us, FP64
+// Helmholtz (a few) 15.1 -> 7.2, FP32 periodic (means removed) 26.1 -> 11.2;
+// a batch's 512 problems 30 -> 17.5 us.  (The columns of the tail as one
+// 1024 x 1024 matrix, applied by all CUs, would be faster still, but its
+// rounding differs: histories near the residual floor no longer follow the
+// step-by-step arithmetic.)
+namespace {
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// value of the lane D to the right / left in the row of 16 lanes (rotating)
+template <int D, typename T>
+__device__ __forceinline__ T from_right16(T v) { return dpp<0x120 + 16 - D>(v); }
+template <int D, typename T>
+__device__ __forceinline__ T from_left16(T v) { return dpp<0x120 + D>(v); }
+// value of the other lane of a pair (quad_perm 1 0 3 2), of lane Q of the quad
+template <typename T>
+__device__ __forceinline__ T pair_swap(T v) { return dpp<0xB1>(v); }
+template <int Q, typename T>
+__device__ __forceinline__ T quad_lane(T v) { return dpp<Q * 0x55>(v); }
+// value of lane addr / 4
+__device__ __forceinline__ float lane_at(int addr, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_at(int addr, double v) {
+    const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(v));
+    const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(v));
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ float lane_const(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_const(double v, int l) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
+// Sum of v over the wave's lanes whose index within a row of 16 is a multiple
+// of 16 / N (N distinct values a row): rotations within the rows, then the
+// four rows in order.  Every lane gets the result.
+template <int N>
+__device__ __forceinline__ double wave_total(double v) {
+    if constexpr (N >= 16) v += dpp<0x121>(v);
+    if constexpr (N >= 8) v += dpp<0x122>(v);
+    v += dpp<0x124>(v);
+    v += dpp<0x128>(v);
+    return ((lane_const(v, 0) + lane_const(v, 16)) + lane_const(v, 32)) + lane_const(v, 48);
+}
+
+// Side rules and this lane's place, for the whole kernel.
+template <typename T>
+struct TailSides {
+    bool px, py;
+    T sxl, sxh, syl, syh;
+    int up, dn;            // ds_bpermute addresses of lanes + 16, - 16 (wrapping)
+    bool odd;              // I odd
+    int I, g;
+    // ghost of a neighbour outside the domain, else the neighbour
+    __device__ __forceinline__ T west(bool edge, T self, T w) const { return !px && edge ? sxl * self : w; }
+    __device__ __forceinline__ T east(bool edge, T self, T e) const { return !px && edge ? sxh * self : e; }
+    __device__ __forceinline__ T south(bool edge, T self, T s) const { return !py && edge ? syl * self : s; }
+    __device__ __forceinline__ T north(bool edge, T self, T n) const { return !py && edge ? syh * self : n; }
+};
+
+template <typename T>
+struct OpConst {
+    T cc, invd, alpha, beta, ih2;
+    __device__ __forceinline__ T relax(T f, T e, T w, T nn, T s) const {
+        return (f + cc * (((e + w) + nn) + s)) * invd;
+    }
+    __device__ __forceinline__ T resid(T f, T p, T e, T w, T nn, T s) const {
+        const T lap = ((((e - p) + (w - p)) + (nn - p)) + (s - p)) * ih2;
+        return f - (alpha * p - beta * lap);
+    }
+};
+
+// prolongated correction at the fine cell of quarter offsets dx, dy
+template <typename T>
+__device__ __forceinline__ T slopes(T e, T ee, T ew, T en, T es, T dx, T dy) {
+    const T mx = T(0.5) * (ee - ew), my = T(0.5) * (en - es);
+    return (e + dx * mx) + dy * my;
+}
+
+// ---- 32 x 32
+template <typename T>
+__device__ __forceinline__ void relax32(T (&P)[2][8], const T (&F)[2][8], const TailSides<T> &sd, const OpConst<T> &k,
+                                        int iters) {
+    const bool xl = sd.I == 0, xh = sd.I == 15;
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int colour = 0; colour < 2; ++colour) {
+            // row r updates column (r + colour) % 2
+            const T below = lane_at(sd.dn, P[colour][7]), above = lane_at(sd.up, P[1 - colour][0]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int c = (r + colour) & 1;
+                const T self = P[c][r];
+                T e = c ? from_right16<1>(P[0][r]) : P[1][r];
+                T w = c ? P[0][r] : from_left16<1>(P[1][r]);
+                if (c) e = sd.east(xh, self, e);
+                else w = sd.west(xl, self, w);
+                const T nn = r < 7 ? P[c][r < 7 ? r + 1 : 7] : sd.north(sd.g == 3, self, above);
+                const T s = r > 0 ? P[c][r > 0 ? r - 1 : 0] : sd.south(sd.g == 0, self, below);
+                P[c][r] = k.relax(F[c][r], e, w, nn, s);
+            }
+        }
+    }
+}
+
+// ---- 16 x 16: R[j], B[j] are the lane's red and black cells of rows 2j, 2j + 1
+template <int COLOUR, typename T>
+__device__ __forceinline__ void sweep16(T (&A)[2], const T (&O)[2], const T (&F)[2], const TailSides<T> &sd,
+                                        const OpConst<T> &k) {
+    // a cell of this colour lies in row 2j + q, q = (I + COLOUR) % 2; its
+    // vertical neighbours are O[j] and the O of the row pair below (q = 0) or
+    // above (q = 1)
+    const bool q = sd.odd != (COLOUR == 1);
+    const T ext = lane_at(q ? sd.up : sd.dn, q ? O[0] : O[1]);
+    const bool xl = sd.I == 0, xh = sd.I == 15;
+    T n[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const T self = A[j];
+        const T e = sd.east(xh, self, from_right16<1>(O[j])), w = sd.west(xl, self, from_left16<1>(O[j]));
+        T nn = q ? (j == 0 ? O[1] : ext) : O[j];
+        T s = q ? O[j] : (j == 0 ? ext : O[0]);
+        if (j == 1) nn = sd.north(q && sd.g == 3, self, nn);
+        if (j == 0) s = sd.south(!q && sd.g == 0, self, s);
+        n[j] = k.relax(F[j], e, w, nn, s);
+    }
+    A[0] = n[0];
+    A[1] = n[1];
+}
+template <typename T>
+__device__ __forceinline__ void relax16(T (&R)[2], T (&B)[2], const T (&FR)[2], const T (&FB)[2], const TailSides<T> &sd,
+                                        const OpConst<T> &k, int iters) {
+    for (int it = 0; it < iters; ++it) {
+        sweep16<0>(R, B, FR, sd, k);
+        sweep16<1>(B, R, FB, sd, k);
+    }
+}
+// rows in order <-> red and black cells
+template <typename T>
+__device__ __forceinline__ void rows_of(const T (&R)[2], const T (&B)[2], bool odd, T (&row)[4]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        row[2 * j] = odd ? B[j] : R[j];
+        row[2 * j + 1] = odd ? R[j] : B[j];
+    }
+}
+template <typename T>
+__device__ __forceinline__ void colours_of(const T (&row)[4], bool odd, T (&R)[2], T (&B)[2]) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        R[j] = odd ? row[2 * j + 1] : row[2 * j];
+        B[j] = odd ? row[2 * j] : row[2 * j + 1];
+    }
+}
+
+// ---- 8 x 8: one cell per lane
+template <typename T>
+struct Nb {
+    T e, w, n, s;
+};
+template <typename T>
+__device__ __forceinline__ Nb<T> neighbours8(T p, const TailSides<T> &sd) {
+    const T other = lane_at((((threadIdx.x & 63) + (sd.odd ? 15 : 49)) & 63) * 4, p);  // lane + 16 - 1 / lane - 16 + 1
+    const T pair = pair_swap(p);
+    Nb<T> v;
+    v.e = sd.east(sd.I >= 14, p, from_right16<2>(p));
+    v.w = sd.west(sd.I < 2, p, from_left16<2>(p));
+    v.n = sd.north(sd.odd && sd.g == 3, p, sd.odd ? other : pair);
+    v.s = sd.south(!sd.odd && sd.g == 0, p, sd.odd ? pair : other);
+    return v;
+}
+template <typename T>
+__device__ __forceinline__ Nb<T> neighbours4(T p, const TailSides<T> &sd) {
+    Nb<T> v;
+    v.e = sd.east(sd.I >= 12, p, from_right16<4>(p));
+    v.w = sd.west(sd.I < 4, p, from_left16<4>(p));
+    v.n = sd.north(sd.g == 3, p, lane_at(sd.up, p));
+    v.s = sd.south(sd.g == 0, p, lane_at(sd.dn, p));
+    return v;
+}
+// N = 8 or 4
+template <int N, typename T>
+__device__ __forceinline__ void relax1(T &p, T f, const TailSides<T> &sd, const OpConst<T> &k, int iters) {
+    const int x = N == 8 ? sd.I >> 1 : sd.I >> 2, y = N == 8 ? 2 * sd.g + (sd.I & 1) : sd.g;
+    const bool red = ((x + y) & 1) == 0;
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int colour = 0; colour < 2; ++colour) {
+            const Nb<T> v = N == 8 ? neighbours8(p, sd) : neighbours4(p, sd);
+            const T q = k.relax(f, v.e, v.w, v.n, v.s);
+            p = red == (colour == 0) ? q : p;
+        }
+    }
+}
+
+// Exact bottom on the 8 x 8 or 4 x 4 level held one cell per lane: cell i =
+// sum_j ainv[j m + i] f_j in FP64, j in order (f_j is the value of lane_of(j)).
+template <int N, typename T>
+__device__ __forceinline__ T exact_bottom(const double *__restrict__ ainv, T f, const TailSides<T> &sd) {
+    constexpr int M = N * N;
+    const int i = N == 8 ? (2 * sd.g + (sd.I & 1)) * 8 + (sd.I >> 1) : (threadIdx.x & 63) >> 2;
+    double s = 0.0;
+#pragma unroll
+    for (int j0 = 0; j0 < M; j0 += 16) {
+        double a[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] = ainv[(j0 + j) * M + i];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int q = j0 + j, y = q >> 3, x = q & 7;
+            const int l = N == 8 ? 16 * (y >> 1) + 2 * x + (y & 1) : 4 * q;
+            s += a[j] * (double)lane_const(f, l);
+        }
+    }
+    return T(s);
+}
+
+template <typename T>
+__device__ void tail_body(const CoarseArgs<T> &a) {
+    const int lane = threadIdx.x & 63;
+    TailSides<T> sd;
+    sd.px = a.bc[CCMG_XLO] == CCMG_BC_PERIODIC;
+    sd.py = a.bc[CCMG_YLO] == CCMG_BC_PERIODIC;
+    sd.sxl = a.bc[CCMG_XLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.sxh = a.bc[CCMG_XHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.syl = a.bc[CCMG_YLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.syh = a.bc[CCMG_YHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.I = lane & 15;
+    sd.g = lane >> 4;
+    sd.odd = lane & 1;
+    sd.up = ((lane + 16) & 63) * 4;
+    sd.dn = ((lane + 48) & 63) * 4;
+    auto consts = [&](int l) {
+        return OpConst<T>{T(a.cc[l]), T(a.invd[l]), T(a.alpha), T(a.beta), T(a.ih2[l])};
+    };
+    // 32 x 32: every load before the skip flag is looked at
+    T P5[2][8], F5[2][8];
+    const int stop = a.skip ? *a.skip : 0;
+    const double shift64 = (a.load_phi && a.phi_shift) ? *a.phi_shift : 0.0;
+    {
+        const T *f = a.f + (long)(8 * sd.g + 1) * a.pf + 1 + 2 * sd.I;
+        const T *p = a.phi_in + (long)(8 * sd.g + 1) * a.pin + 1 + 2 * sd.I;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            F5[0][r] = f[(long)r * a.pf];
+            F5[1][r] = f[(long)r * a.pf + 1];
+        }
+        if (a.load_phi) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                P5[0][r] = p[(long)r * a.pin];
+                P5[1][r] = p[(long)r * a.pin + 1];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) P5[0][r] = P5[1][r] = T(0);
+        }
+    }
+    if (stop) return;
+    const T shift = T(shift64);
+    if (a.load_phi) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            P5[0][r] -= shift;
+            P5[1][r] -= shift;
+        }
+    }
+    if (a.sub_top_mean) {
+        double t = 0.0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) t += (double)F5[0][r] + (double)F5[1][r];
+        const T m = T(wave_total<16>(t) / 1024.0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            F5[0][r] -= m;
+            F5[1][r] -= m;
+        }
+    }
+    const OpConst<T> k5 = consts(0), k4 = consts(1), k3 = consts(2), k2 = consts(3);
+    const bool xl = sd.I == 0, xh = sd.I == 15;
+    relax32(P5, F5, sd, k5, a.nu1);
+    // residual and restriction 32 -> 16
+    T frow[4];
+    {
+        T below[2], above[2], res[2][8];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            below[c] = lane_at(sd.dn, P5[c][7]);
+            above[c] = lane_at(sd.up, P5[c][0]);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const T self = P5[c][r];
+                const T e = c ? sd.east(xh, self, from_right16<1>(P5[0][r])) : P5[1][r];
+                const T w = c ? P5[0][r] : sd.west(xl, self, from_left16<1>(P5[1][r]));
+                const T nn = r < 7 ? P5[c][r < 7 ? r + 1 : 7] : sd.north(sd.g == 3, self, above[c]);
+                const T s = r > 0 ? P5[c][r > 0 ? r - 1 : 0] : sd.south(sd.g == 0, self, below[c]);
+                res[c][r] = k5.resid(F5[c][r], self, e, w, nn, s);
+            }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            frow[j] = T(0.25) * (((res[0][2 * j] + res[1][2 * j]) + res[0][2 * j + 1]) + res[1][2 * j + 1]);
+        if (a.singular) {
+            const double t = (((double)frow[0] + (double)frow[1]) + (double)frow[2]) + (double)frow[3];
+            const T m = T(wave_total<16>(t) / 256.0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) frow[j] -= m;
+        }
+    }
+    // 16 x 16
+    T R4[2] = {T(0), T(0)}, B4[2] = {T(0), T(0)}, FR4[2], FB4[2];
+    colours_of(frow, sd.odd, FR4, FB4);
+    relax16(R4, B4, FR4, FB4, sd, k4, a.nu1);
+    T f3;
+    {
+        T p[4], res[4];
+        rows_of(R4, B4, sd.odd, p);
+        const T below = lane_at(sd.dn, p[3]), above = lane_at(sd.up, p[0]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const T e = sd.east(xh, p[r], from_right16<1>(p[r])), w = sd.west(xl, p[r], from_left16<1>(p[r]));
+            const T nn = r < 3 ? p[r < 3 ? r + 1 : 3] : sd.north(sd.g == 3, p[r], above);
+            const T s = r > 0 ? p[r > 0 ? r - 1 : 0] : sd.south(sd.g == 0, p[r], below);
+            res[r] = k4.resid(frow[r], p[r], e, w, nn, s);
+        }
+        // the pair's four cells: rows 0, 1 in the even lane, 2, 3 in the odd one
+        const T o0 = pair_swap(sd.odd ? res[0] : res[2]), o1 = pair_swap(sd.odd ? res[1] : res[3]);
+        const T r00 = sd.odd ? o0 : res[0], r01 = sd.odd ? res[2] : o0;
+        const T r10 = sd.odd ? o1 : res[1], r11 = sd.odd ? res[3] : o1;
+        f3 = T(0.25) * (((r00 + r01) + r10) + r11);
+        if (a.singular) f3 -= T(wave_total<16>((double)f3) / 64.0);
+    }
+    // 8 x 8
+    T p3 = T(0);
+    if (a.n_bottom == 8) {
+        p3 = exact_bottom<8>(a.ainv, f3, sd);
+    } else {
+        relax1<8>(p3, f3, sd, k3, a.nu1);
+        T f2;
+        {
+            const Nb<T> v = neighbours8(p3, sd);
+            const T res = k3.resid(f3, p3, v.e, v.w, v.n, v.s);
+            f2 = T(0.25) * (((quad_lane<0>(res) + quad_lane<2>(res)) + quad_lane<1>(res)) + quad_lane<3>(res));
+            if (a.singular) f2 -= T(wave_total<4>((double)f2) / 16.0);
+        }
+        // 4 x 4
+        T p2 = T(0);
+        if (a.n_bottom == 4) {
+            p2 = exact_bottom<4>(a.ainv, f2, sd);
+        } else {
+            relax1<4>(p2, f2, sd, k2, a.nu1);
+            // residual and restriction 4 -> 2, the 2 x 2 grid in every lane
+            T f1[4], p1[4];
+            {
+                const Nb<T> v = neighbours4(p2, sd);
+                const T res = k2.resid(f2, p2, v.e, v.w, v.n, v.s);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int l = 32 * (q >> 1) + 8 * (q & 1);  // lane of the block's first cell
+                    f1[q] = T(0.25) * (((lane_const(res, l) + lane_const(res, l + 4)) + lane_const(res, l + 16)) +
+                                       lane_const(res, l + 20));
+                }
+                if (a.singular) {
+                    const T m = T(((((double)f1[0] + (double)f1[1]) + (double)f1[2]) + (double)f1[3]) / 4.0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) f1[q] -= m;
+                }
+            }
+            {
+                const double fd[4] = {(double)f1[0], (double)f1[1], (double)f1[2], (double)f1[3]};
+                double pd[4] = {0.0, 0.0, 0.0, 0.0};
+                relax2(a.cc[4], a.invd[4], a.nu_bottom, sd.px, sd.py, sd.sxl, sd.sxh, sd.syl, sd.syh, fd, pd);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) p1[q] = T(pd[q]);
+            }
+            // prolongation 2 -> 4
+            const int C = sd.I >> 2, X = C >> 1, Y = sd.g >> 1;
+            const T own = Y ? (X ? p1[3] : p1[2]) : (X ? p1[1] : p1[0]);
+            const T ox = Y ? (X ? p1[2] : p1[3]) : (X ? p1[0] : p1[1]);
+            const T oy = Y ? (X ? p1[1] : p1[0]) : (X ? p1[3] : p1[2]);
+            const T ee = X ? sd.east(true, own, ox) : ox, ew = X ? ox : sd.west(true, own, ox);
+            const T en = Y ? sd.north(true, own, oy) : oy, es = Y ? oy : sd.south(true, own, oy);
+            p2 = p2 + slopes(own, ee, ew, en, es, (C & 1) ? T(0.25) : T(-0.25), (sd.g & 1) ? T(0.25) : T(-0.25));
+            relax1<4>(p2, f2, sd, k2, a.nu2);
+        }
+        // prolongation 4 -> 8: the coarse cell is the quad's
+        {
+            const Nb<T> v = neighbours4(p2, sd);
+            p3 = p3 + slopes(p2, v.e, v.w, v.n, v.s, (sd.I & 2) ? T(0.25) : T(-0.25), sd.odd ? T(0.25) : T(-0.25));
+        }
+        relax1<8>(p3, f3, sd, k3, a.nu2);
+    }
+    // prolongation 8 -> 16: coarse rows 2g (even lane of the pair) and 2g + 1 (odd lane)
+    {
+        const T sw = pair_swap(p3);
+        const T E[2] = {sd.odd ? sw : p3, sd.odd ? p3 : sw};
+        const T below = lane_at(sd.dn, E[1]), above = lane_at(sd.up, E[0]);
+        const T dx = sd.odd ? T(0.25) : T(-0.25);
+        T p[4];
+        rows_of(R4, B4, sd.odd, p);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const T ee = sd.east(sd.I >= 14, E[q], from_right16<2>(E[q])), ew = sd.west(sd.I < 2, E[q], from_left16<2>(E[q]));
+            const T en = q == 0 ? E[1] : sd.north(sd.g == 3, E[1], above);
+            const T es = q == 1 ? E[0] : sd.south(sd.g == 0, E[0], below);
+            p[2 * q] = p[2 * q] + slopes(E[q], ee, ew, en, es, dx, T(-0.25));
+            p[2 * q + 1] = p[2 * q + 1] + slopes(E[q], ee, ew, en, es, dx, T(0.25));
+        }
+        colours_of(p, sd.odd, R4, B4);
+    }
+    relax16(R4, B4, FR4, FB4, sd, k4, a.nu2);
+    // prolongation 16 -> 32: the lane's own column and rows
+    {
+        T E[4];
+        rows_of(R4, B4, sd.odd, E);
+        const T below = lane_at(sd.dn, E[3]), above = lane_at(sd.up, E[0]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T ee = sd.east(xh, E[q], from_right16<1>(E[q])), ew = sd.west(xl, E[q], from_left16<1>(E[q]));
+            const T en = q < 3 ? E[q < 3 ? q + 1 : 3] : sd.north(sd.g == 3, E[3], above);
+            const T es = q > 0 ? E[q > 0 ? q - 1 : 0] : sd.south(sd.g == 0, E[0], below);
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    P5[c][2 * q + h] = P5[c][2 * q + h] + slopes(E[q], ee, ew, en, es, c ? T(0.25) : T(-0.25),
+                                                                 h ? T(0.25) : T(-0.25));
+        }
+    }
+    relax32(P5, F5, sd, k5, a.nu2);
+    T *o = a.phi_out + (long)(8 * sd.g + 1) * a.pout + 1 + 2 * sd.I;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        o[(long)r * a.pout] = P5[0][r];
+        o[(long)r * a.pout + 1] = P5[1][r];
+    }
+}
+
+}  // namespace
+
+template <typename T>
+__global__ __launch_bounds__(64) void k_tail(const CoarseArgs<T> a) {
+    tail_body<T>(a);
+}
+
 template <int NT, typename T, bool DIRECT>
 __global__ __launch_bounds__(NT) void k_coarse(const CoarseArgs<T> a) {
     coarse_body<NT, T, DIRECT>(a);
 }
 
-// Batches: one workgroup per problem (relaxation bottom).
-template <int NT, typename T>
-__global__ __launch_bounds__(NT) void k_coarse_list(const CoarseArgs<T> *__restrict__ list) {
-    coarse_body<NT, T, false>(list[blockIdx.x]);
+// Batches: one wavefront per problem (relaxation bottom).
+template <typename T>
+__global__ __launch_bounds__(64) void k_coarse_list(const CoarseArgs<T> *__restrict__ list) {
+    const CoarseArgs<T> &a = list[blockIdx.x];
+    if (a.n_top == kCoarseMax) tail_body<T>(a);
+    else coarse_body<64, T, false>(a);
 }
 
 // Inverse of a small level's operator by Gauss-Jordan elimination on [A | I]
@@ -388,7 +890,12 @@ hipError_t launch_coarse(const CoarseArgs<T> &a0, hipStream_t s) {
     const bool direct = a.n_bottom >= 4;
     if (direct && (a.n_bottom > kDirectMax || a.n_bottom > a.n_top || (a.n_bottom & (a.n_bottom - 1)) || !a.ainv))
         return hipErrorInvalidValue;
-    constexpr int NT = kCoarseThreads;
+    if (a.n_top == kCoarseMax) {
+        if (!direct) a.n_bottom = 0;
+        hipLaunchKernelGGL(k_tail<T>, dim3(1), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
+    constexpr int NT = kCoarseThreads;  // smaller finest levels
     if (direct) hipLaunchKernelGGL((k_coarse<NT, T, true>), dim3(1), dim3(NT), 0, s, a);
     else hipLaunchKernelGGL((k_coarse<NT, T, false>), dim3(1), dim3(NT), 0, s, a);
     return hipGetLastError();
@@ -397,7 +904,7 @@ hipError_t launch_coarse(const CoarseArgs<T> &a0, hipStream_t s) {
 template <typename T>
 hipError_t launch_coarse_list(const CoarseArgs<T> *list, int count, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_coarse_list<kCoarseThreads, T>), dim3(count), dim3(kCoarseThreads), 0, s, list);
+    hipLaunchKernelGGL(k_coarse_list<T>, dim3(count), dim3(64), 0, s, list);
     return hipGetLastError();
 }
 
