@@ -436,7 +436,7 @@ int ccmg_solve_learned(ccmg_plan *plan, ccmg_net *net, const double *d_f, double
 
 /* ---- launch-shape autotuning.
  * Times every candidate tile shape (rows per wavefront band x wavefronts per
- * workgroup, or the 2-D tile kernel below the finest level) of the two
+ * workgroup; bands of 8 and 16 rows are held in registers whole) of the two
  * launches of each level, of the same level run as a visit (see
  * CCMG_OPT_VISIT; the visit is kept where its pair is faster), and of the
  * fused finest launch, on the given data and keeps the fastest for this plan.
@@ -445,11 +445,11 @@ int ccmg_solve_learned(ccmg_plan *plan, ccmg_net *net, const double *d_f, double
 int ccmg_plan_autotune(ccmg_plan *plan, const double *d_f, double *d_phi, ptrdiff_t pitch);
 /* Set one launch shape by hand: kind 0 = the nu1 (restricting) launch of
  * `level`, 1 = the nu2 (prolongating) launch; ty even, >= 8 unless it covers
- * the level; 1 <= wpb <= 4.  ty = 0 selects the 2-D LDS tile kernel instead
- * of the row march (levels below the finest with at least 64 cells per side
- * that are not in the one-workgroup tail).  kind 2 = the fused finest launch
- * of FP64 solves, 3 = its FP32 form in mixed-precision steps (level 0 only,
- * ty even and >= 8, no tile kernel).  Levels below the finest that are not
+ * the level; 1 <= wpb <= 4 (bands of 8 and 16 rows that are held in registers
+ * whole run one wave per workgroup).  ty = 0 runs as ty = 8 (levels below the
+ * finest with at least 64 cells per side that are not in the one-workgroup
+ * tail).  kind 2 = the fused finest launch of FP64 solves, 3 = its FP32 form in
+ * mixed-precision steps (level 0 only, ty even and >= 8).  Levels below the finest that are not
  * in the tail, run as a visit (CCMG_OPT_VISIT): kind 4 = the restricting
  * launch without the stored iterate (as kind 0), kind 5 = the visit launch
  * (row march only, ty even and >= 16 unless it covers the level; ty = 0 sets

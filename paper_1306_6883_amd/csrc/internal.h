@@ -120,22 +120,20 @@ constexpr int edge_band_rows(int ty) { return ((ty / 2) + 1) & ~1; }
 
 // Launch description chosen by the host for one level.
 struct MarchShape {
-    int ty;       // rows per tile (even); 0: the 2-D LDS tile kernel (tile.hip)
+    int ty;       // rows per tile (even); 8 and 16 (and 0, as 8): held in registers whole where block_impl.h has the variant
     int wpb;      // waves per workgroup
 };
-
-// The 2-D LDS tile kernel (levels below the finest, n >= kTileMinN): the same
-// launches as the row march for POST_NONE / POST_RESTRICT without a phi shift.
-constexpr int kTileMinN = 64;
-template <typename T>
-hipError_t launch_tile(const MarchArgs<T> &a, int nu, bool load_phi, bool prolong, int post, hipStream_t s,
-                       int *ntiles_out);
 
 // Host launchers (march.hip).  nu in {0,1,2}; load_phi=false means phi starts at 0.
 // *ntiles_out receives the number of tiles (= partial-sum slots) of the launch.
 template <typename T>
 hipError_t launch_march(const MarchArgs<T> &a, int nu, bool load_phi, bool prolong, int post,
                         MarchShape shape, hipStream_t s, int *ntiles_out);
+// The launches of V(2,2) in bands of R = 8 or 16 rows held in registers whole
+// (block_impl.h); hipErrorNotSupported where the row march has to run.
+template <typename T, int R>
+hipError_t dispatch_block(const MarchArgs<T> &a, int nu, bool load_phi, bool prolong, int post, int wpb,
+                          hipStream_t s, int *nt);
 // The fused finest-level launch (POST_FUSED; march_f64_fused.hip).
 hipError_t dispatch_fused(const MarchArgs<double> &a, MarchShape sh, hipStream_t s, int *nt);
 hipError_t dispatch_fused(const MarchArgs<float> &a, MarchShape sh, hipStream_t s, int *nt);

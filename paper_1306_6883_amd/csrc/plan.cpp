@@ -128,9 +128,8 @@ bool build_layout(const ccmg_problem &p, Layout &lay) {
             v.a = take(bytes);
             v.b = take(bytes);
             v.f = take(bytes);
-            // partial sums from the launch on the level above: row-march tiles
-            // or 32 x 32 blocks of the 2-D tile kernel ((2n / 32)^2)
-            v.fpart_cap = std::max(max_tiles(v.n * 2), (v.n / 16) * (v.n / 16));
+            // partial sums from the launch on the level above, one per tile
+            v.fpart_cap = max_tiles(v.n * 2);
             v.fpart = take(sizeof(double) * v.fpart_cap);
         }
     }
@@ -163,6 +162,22 @@ MarchShape shape_for(int n) {
     s.ty = ty < n ? ty : n;
     if (s.ty < 2) s.ty = 2;
     return s;
+}
+
+// Default rows per band of a V(2,2) level's launches and of the fused finest
+// launch: bands held in registers (block_impl.h) as far as they were the
+// faster ones -- the two launches of a level up to 2048^2 (8 rows to 512^2,
+// where every wave counts; from 1024^2 16 rows measure the same and read fewer
+// halo rows), the fused launch up to 1024^2 in FP64 (per cycle of 512^2 56 us
+// against 68 - 102 in marched bands, of 1024^2 86.5 against 89 - 125, of
+// 2048^2 127.6 against 120) and 2048^2 in FP32.
+MarchShape level_shape_for(int n) {
+    if (n < 64 || n > 2048) return shape_for(n);
+    return n >= 1024 ? MarchShape{16, 4} : MarchShape{8, 1};
+}
+MarchShape fused_shape_for(int n, bool f64) {
+    if (n < 64 || n > (f64 ? 1024 : 2048)) return n == 2048 ? MarchShape{64, 1} : shape_for(n);
+    return n >= 1024 ? MarchShape{f64 ? 8 : 16, 4} : MarchShape{8, 1};
 }
 
 // Default shape of a visit launch: its bands carry 8 halo rows on either
@@ -959,14 +974,14 @@ void plan_init_host(ccmg_plan *P, const ccmg_problem &p) {
     P->singular = p.alpha == 0.0 && p.bc[0] != CCMG_BC_DIRICHLET && p.bc[1] != CCMG_BC_DIRICHLET &&
                   p.bc[2] != CCMG_BC_DIRICHLET && p.bc[3] != CCMG_BC_DIRICHLET;
     for (int l = 0; l < P->lay.L && l < kMaxLevels; ++l) {
-        P->shp_pre[l] = P->shp_post[l] = P->shp_pre_v[l] = shape_for(P->lay.lev[l].n);
+        P->shp_pre[l] = P->shp_post[l] = P->shp_pre_v[l] = level_shape_for(P->lay.lev[l].n);
         P->shp_visit[l] = visit_shape_for(P->lay.lev[l].n);
         P->visit[l] = false;
     }
-    P->shp_fused = shape_for(P->lay.lev[0].n);
+    P->shp_fused = fused_shape_for(P->lay.lev[0].n, true);
     P->shp_fused0 = shape_for(P->lay.lev[0].n);
     P->fused0 = false;
-    P->shp_fused32 = shape_for(P->lay.lev[0].n);
+    P->shp_fused32 = fused_shape_for(P->lay.lev[0].n, false);
     P->n_bottom = 2;
     P->tcycle = 0;
     P->timer.on = false;
@@ -1146,15 +1161,30 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
     // change the timing, but keep them finite)
     // (all but the exact bottom's inverse, the last region, which is kept)
     hipError_t err = hipMemsetAsync(P->ws, 0, lay.ainv, s);
-    const int tys[] = {0, 8, 16, 32, 64, 128, 256};
+    const int tys[] = {8, 16, 32, 64, 128, 256};
     const int wpbs[] = {1, 2, 4};
-    const int reps = 4;
+    // A launch of a small level takes about as long as the host takes to
+    // queue it: there more launches are timed, behind a queue of untimed ones.
+    auto reps_for = [](int n) { return n <= 2048 ? 12 : 4; };
+    auto warm_for = [](int n) { return n <= 2048 ? 6 : 1; };
+    // Singular plans: every wave of a level's launches adds the partial sums of
+    // the launch that restricted into it (timed here too, with as many as that
+    // launch writes: `sums`).  So a restricting launch is charged for what its
+    // sums cost the two launches of the next level, about 1 us for each 1024
+    // beyond the first (a round trip to memory).
+    int sums = 0;
+    auto sums_cost = [&](int count, int reps) -> float {
+        return P->singular ? 2.0e-3f * (float)reps * std::max(0.f, (float)count / 1024.f - 1.f) : 0.f;
+    };
     for (int l = 0; l < lay.lt && err == hipSuccess; ++l) {
-        const int n = lay.lev[l].n;
+        const int n = lay.lev[l].n, reps = reps_for(n), warm = warm_for(n);
+        int sums_next = 0;
         // kinds 0 / 1: the level's restricting and prolongating launches;
         // 2 / 3: the same level as a visit (restricting launch without the
-        // stored iterate, visit launch), on levels where a visit applies
-        const bool visit_ok = l >= 1 && P->p.nu1 == 2 && P->p.nu2 == 2;
+        // stored iterate, visit launch), on levels where a visit applies and
+        // can win: below 2048^2 the two launches of bands held in registers
+        // take 12 - 15 us together, a visit's two 20 - 24
+        const bool visit_ok = l >= 1 && n >= 2048 && P->p.nu1 == 2 && P->p.nu2 == 2;
         float kbest[4] = {0.f, 0.f, 0.f, 0.f};
         for (int kind = 0; kind < (visit_ok ? 4 : 2) && err == hipSuccess; ++kind) {
             MarchArgs<T> a{};
@@ -1165,6 +1195,10 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
             } else {
                 a.f = P->at<T>(lay.lev[l].f);
                 a.pf = lay.lev[l].pitch;
+            }
+            if (P->singular && l > 0) {
+                a.fmean_part = P->at<double>(lay.lev[l].fpart);
+                a.fmean_count = sums;
             }
             const bool caller_phi = l == 0 && f64;
             T *pa = caller_phi ? reinterpret_cast<T *>(d_phi) : P->at<T>(lay.lev[l].a);
@@ -1220,27 +1254,34 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
             float best = 1e30f;
             MarchShape *const slot[4] = {&P->shp_pre[l], &P->shp_post[l], &P->shp_pre_v[l], &P->shp_visit[l]};
             MarchShape bs = *slot[kind];
-            // candidates: row-march shapes (powers of two, and bands that
-            // balance the waves over the SIMDs), and (levels below the finest)
-            // the 2-D LDS tile kernel, written as ty = 0 (not for the visit
-            // launch, whose bands need 8 halo rows a side: none below 16 rows)
-            const bool tile_ok = l > 0 && n >= kTileMinN && kind != 3;
+            // candidates: powers of two, and bands that balance the waves
+            // over the SIMDs (not below 16 rows for the visit launch, whose
+            // bands need 8 halo rows a side); where bands held in registers
+            // are always the faster ones, only those, and of them no choice
+            // to 512^2: 8 rows by one wave measured the best there, by less
+            // than two timings of one launch differ
+            const bool held_ok = kind != 3 && nu == 2 && post != POST_IR;
             std::vector<MarchShape> cands;
             for (int ty : tys) {
-                if (ty == 0) {
-                    if (tile_ok) cands.push_back(MarchShape{0, 1});
+                if (ty > n || (kind == 3 && ty < 16 && ty < n)) continue;
+                const bool held = ty <= 16 && held_ok;
+                if (held_ok && n >= 64 && n <= 2048 && !held) continue;
+                if (held_ok && n >= 64 && n <= 512) {
+                    if (cands.empty()) cands.push_back(MarchShape{8, 1});
                     continue;
                 }
-                if (ty > n || (kind == 3 && ty < 16 && ty < n)) continue;
-                for (int wpb : wpbs) cands.push_back(MarchShape{ty < n ? ty : n, wpb});
+                for (int wpb : wpbs)
+                    if (wpb != 2 || !held) cands.push_back(MarchShape{ty < n ? ty : n, wpb});
             }
             const bool res = post != POST_NONE && post != POST_VISIT;
-            for (int ty : balanced_tys(n, march_outw(nu, prolong, res), P->simds, 4, xwalls))
-                if (kind != 3 || ty >= 16) cands.push_back(MarchShape{ty, 1});
+            if (!(held_ok && n >= 64 && n <= 2048))
+                for (int ty : balanced_tys(n, march_outw(nu, prolong, res), P->simds, 4, xwalls))
+                    if (kind != 3 || ty >= 16) cands.push_back(MarchShape{ty, 1});
             for (const MarchShape &sh : cands) {
                 {
-                    int nt;
-                    err = launch_march<T>(a, nu, load_phi, prolong, post, sh, s, &nt);  // warm-up
+                    int nt = 0;
+                    for (int r = 0; r < warm && err == hipSuccess; ++r)
+                        err = launch_march<T>(a, nu, load_phi, prolong, post, sh, s, &nt);
                     if (err == hipSuccess) err = hipEventRecord(e0, s);
                     for (int r = 0; r < reps && err == hipSuccess; ++r)
                         err = launch_march<T>(a, nu, load_phi, prolong, post, sh, s, &nt);
@@ -1249,9 +1290,14 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
                     float ms = 0.f;
                     if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
                     if (err != hipSuccess) break;
+                    if (kind == 0 || kind == 2) ms += sums_cost(nt, reps);
+                    // (the one workgroup that adds f's statistics in a solve's
+                    // first launch: 22 us for 36 k of them, 40 for 73 k)
+                    if (l == 0 && f64) ms += 0.55e-6f * (float)reps * (float)nt;
                     if (ms < best) {
                         best = ms;
                         bs = sh;
+                        if (kind == 0) sums_next = nt;
                     }
                 }
                 if (err != hipSuccess) break;
@@ -1259,14 +1305,14 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
             *slot[kind] = bs;
             kbest[kind] = best;
         }
+        sums = sums_next;
         // the visit pair replaces the two launches where it is faster
         if (err == hipSuccess && l < kMaxLevels) P->visit[l] = visit_ok && kbest[2] + kbest[3] < kbest[0] + kbest[1];
     }
     // Visits, level by level from the top: decided on the coarse part of whole
     // cycles (levels 1 down, as the fused driver runs them), each form timed
     // three times, the faster kept.  A launch timed alone misses how it
-    // shares the caches with its neighbours in the cycle, and the small
-    // levels' launches differ by a few microseconds.
+    // shares the caches with its neighbours in the cycle.
     if (err == hipSuccess && P->p.nu1 == 2 && P->p.nu2 == 2 && lay.lt >= 2) {
         const int saved = P->opt_visit;
         P->opt_visit = 1;
@@ -1287,7 +1333,7 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
             if (x == hipSuccess && ms < *best) *best = ms;
             return x;
         };
-        for (int l = 1; l < lay.lt && l < kMaxLevels && err == hipSuccess; ++l) {
+        for (int l = 1; l < lay.lt && l < kMaxLevels && err == hipSuccess && lay.lev[l].n >= 2048; ++l) {
             float on = 1e30f, off = 1e30f;
             for (int round = 0; round < 3 && err == hipSuccess; ++round) {
                 P->visit[l] = false;
@@ -1326,19 +1372,25 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
         a.aux = P->at<T>(lay.lev[1].f);
         a.paux = lay.lev[1].pitch;
         a.partial = P->at<double>(lay.lev[1].fpart);
-        const int n = lay.lev[0].n;
+        const int n = lay.lev[0].n, reps = reps_for(n), warm = warm_for(n);
         float best = 1e30f;
         MarchShape bs = f64 ? P->shp_fused : P->shp_fused32;
         std::vector<MarchShape> cands;
-        for (int ty : {16, 32, 64, 128, 256}) {
+        for (int ty : {8, 16, 32, 64, 128, 256}) {
             if (ty > n && ty != 16) continue;
-            for (int wpb : {1, 2}) cands.push_back(MarchShape{ty < n ? ty : n, wpb});
+            if (n >= 64 && n <= (f64 ? 512 : 1024) && ty > 16) continue;  // held in registers, always the faster
+            const bool held = ty == 8 || (ty == 16 && !f64);
+            for (int wpb : {1, 2, 4})
+                if (wpb == 1 || wpb == (held ? 4 : 2)) cands.push_back(MarchShape{ty < n ? ty : n, wpb});
         }
-        for (int ty : balanced_tys(n, march_outw(4, true, true), P->simds, 4, xwalls)) cands.push_back(MarchShape{ty, 1});
+        if (n > (f64 ? 512 : 1024))
+            for (int ty : balanced_tys(n, march_outw(4, true, true), P->simds, 4, xwalls))
+                cands.push_back(MarchShape{ty, 1});
         for (const MarchShape &sh : cands) {
             {
-                int nt;
-                err = launch_march<T>(a, 4, true, true, POST_FUSED, sh, s, &nt);  // warm-up
+                int nt = 0;
+                for (int r = 0; r < warm && err == hipSuccess; ++r)
+                    err = launch_march<T>(a, 4, true, true, POST_FUSED, sh, s, &nt);
                 if (err == hipSuccess) err = hipEventRecord(e0, s);
                 for (int r = 0; r < reps && err == hipSuccess; ++r)
                     err = launch_march<T>(a, 4, true, true, POST_FUSED, sh, s, &nt);
@@ -1347,6 +1399,7 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
                 float ms = 0.f;
                 if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
                 if (err != hipSuccess) break;
+                ms += sums_cost(nt, reps);
                 if (ms < best) {
                     best = ms;
                     bs = sh;
@@ -1462,8 +1515,8 @@ int ccmg_plan_set_shape(ccmg_plan *P, int level, int kind, int ty, int wpb) {
         else P->shp_fused32 = sh;
         return CCMG_OK;
     }
-    if (ty == 0) {  // the 2-D LDS tile kernel: levels below the finest that are not in the tail
-        if (level == 0 || level >= P->lay.lt || P->lay.lev[level].n < kTileMinN) return CCMG_EINVAL;
+    if (ty == 0) {  // bands of 8 rows: levels below the finest that are not in the tail
+        if (level == 0 || level >= P->lay.lt) return CCMG_EINVAL;
         (kind == 0 ? P->shp_pre : kind == 1 ? P->shp_post : P->shp_pre_v)[level] = MarchShape{0, 1};
         return CCMG_OK;
     }

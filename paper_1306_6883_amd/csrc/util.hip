@@ -182,14 +182,18 @@ __global__ __launch_bounds__(kRed) void k_fstats_restrict(const double *f, long 
     }
 }
 
-__global__ __launch_bounds__(kRed) void k_reduce4(const double *p, int count, double *out4) {
-    __shared__ double red[4];
+// Sums of `count` quadruples in one workgroup (a launch in bands of 8 or 16
+// rows leaves some ten thousand of them at 8192^2, 0.3 MB): 1024 threads, four
+// quadruples in flight each.
+constexpr int kRed4 = 1024;
+__global__ __launch_bounds__(kRed4) void k_reduce4(const double *p, int count, double *out4) {
+    __shared__ double red[kRed4 / 64][4];
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     int i = threadIdx.x;
-    for (; i + 3 * kRed < count; i += 4 * kRed) {  // four quadruples in flight, added in order
+    for (; i + 3 * kRed4 < count; i += 4 * kRed4) {  // four quadruples in flight, added in order
         double4 v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const double4 *>(p + 4 * (i + k * kRed));
+        for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const double4 *>(p + 4 * (i + k * kRed4));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             s[0] += v[k].x;
@@ -198,30 +202,38 @@ __global__ __launch_bounds__(kRed) void k_reduce4(const double *p, int count, do
             s[3] += v[k].w;
         }
     }
-    for (; i < count; i += kRed)
+    for (; i < count; i += kRed4)
         for (int q = 0; q < 4; ++q) s[q] += p[4 * i + q];
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const double t = block_sum256(s[q], red);
-        if (threadIdx.x == 0) out4[q] = t;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s[q] += __shfl_xor(s[q], off);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = 0.0;
+        for (int w = 0; w < kRed4 / 64; ++w) t += red[w][threadIdx.x];
+        out4[threadIdx.x] = t;
     }
 }
 
 hipError_t launch_reduce4(const double *partial, int count, double *out4, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed), 0, s, partial, count, out4);
+    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed4), 0, s, partial, count, out4);
     return hipGetLastError();
 }
 
 hipError_t launch_fstats(const double *f, long pitch, int n, double *partial, int blocks, double *out4,
                          hipStream_t s) {
     hipLaunchKernelGGL(k_fstats, dim3(blocks), dim3(kRed), 0, s, f, pitch, n, partial);
-    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed), 0, s, partial, blocks, out4);
+    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed4), 0, s, partial, blocks, out4);
     return hipGetLastError();
 }
 
 hipError_t launch_fstats_restrict(const double *f, long pitch, int n, double *partial, int blocks, double *out4,
                                   double *coarse, long pc, hipStream_t s) {
     hipLaunchKernelGGL(k_fstats_restrict, dim3(blocks), dim3(kRed), 0, s, f, pitch, n, partial, coarse, pc);
-    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed), 0, s, partial, blocks, out4);
+    hipLaunchKernelGGL(k_reduce4, dim3(1), dim3(kRed4), 0, s, partial, blocks, out4);
     return hipGetLastError();
 }
 
