@@ -49,36 +49,35 @@ __device__ __forceinline__ int xcd_block() {
 }  // namespace
 
 // out[b][y][x][co] = sum_{tap, ci} w[co][tap][ci] * in[b][y + dy][x + dx][ci]
-// One wavefront per 32 pixels of one row.  An activation is carried as a pair
-// of BF16 values (hi + lo, about 16 significant bits): with `in_lo` the
-// products take two MFMAs (hi and lo against the same BF16 weights), and with
-// `out_lo` the FP32 sum is written as such a pair.  Without them (gradients)
-// one BF16 value.
-// SPLIT = 1: four tiles per workgroup of 256, one per wavefront.  SPLIT = 3
-// (small batches, too few tiles to occupy the GPU): one tile per workgroup of
-// 192; wavefront s takes taps 3s .. 3s + 2 and the first adds the other two's
+// An activation is carried as a pair of BF16 values (hi + lo, about 16
+// significant bits) and so are the weights: a product takes three MFMAs (hi w,
+// lo w, hi w_lo; lo x lo is below the FP32 sums' rounding).  Gradients are one
+// BF16 value, one MFMA.  The FP32 sum runs over tap, then 16 channels, then
+// those products, in that order in both kernels' wavefronts.
+
+// Batches too small to give every CU a few rows (at most kConvSplitMaxBatch
+// images): one 32-pixel tile of a row per workgroup of 192; wavefront s takes
+// taps 3s .. 3s + 2 straight from memory and the first adds the other two's
 // partial sums from LDS, (acc0 + acc1) + acc2.
-template <int SPLIT>
-__global__ __launch_bounds__(256) void k_conv32(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
-                                                const __bf16 *__restrict__ w, const __bf16 *__restrict__ w_lo,
-                                                __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int nb,
-                                                int dil) {
+__global__ __launch_bounds__(192) void k_conv32_split(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
+                                                      const __bf16 *__restrict__ w, const __bf16 *__restrict__ w_lo,
+                                                      __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int nb,
+                                                      int dil) {
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = SPLIT == 1 ? xcd_block() * 4 + wib : xcd_block();
+    const int tileno = xcd_block();
     const int tiles_per_row = kNetG / 32;
-    if (wave >= nb * kNetG * tiles_per_row) return;  // uniform over the workgroup when SPLIT > 1
-    const int b = wave / (kNetG * tiles_per_row);
-    const int rem = wave - b * kNetG * tiles_per_row;
+    if (tileno >= nb * kNetG * tiles_per_row) return;  // uniform over the workgroup
+    const int b = tileno / (kNetG * tiles_per_row);
+    const int rem = tileno - b * kNetG * tiles_per_row;
     const int y = rem / tiles_per_row;
     const int x0 = (rem - y * tiles_per_row) * 32;
     const int r = lane & 31, hk = lane >> 5;
     const size_t img = (size_t)b * kNetG * kNetG * kNetC;
     f32x16 acc = {};
-    const int t0 = SPLIT == 1 ? 0 : 3 * wib;
 #pragma unroll
-    for (int tt = 0; tt < 9 / SPLIT; ++tt) {
-        const int t = t0 + tt;
+    for (int tt = 0; tt < 3; ++tt) {
+        const int t = 3 * wib + tt;
         const int ys = wrapg(y + tap_dy(t, dil));
         const int xs = wrapg(x0 + r + tap_dx(t, dil));
         const size_t px = img + ((size_t)ys * kNetG + xs) * kNetC;
@@ -88,38 +87,170 @@ __global__ __launch_bounds__(256) void k_conv32(const __bf16 *__restrict__ in, c
             const bf16x8 bv = load8(w + wo);
             const bf16x8 av = load8(in + px + 16 * h + 8 * hk);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-            if (in_lo)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(in_lo + px + 16 * h + 8 * hk), bv, acc, 0, 0, 0);
-            if (w_lo)  // the weights' low parts (hi activations; lo x lo is below the FP32 sums' rounding)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, load8(w_lo + wo), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(in_lo + px + 16 * h + 8 * hk), bv, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, load8(w_lo + wo), acc, 0, 0, 0);
         }
     }
-    if constexpr (SPLIT > 1) {
-        __shared__ float part[SPLIT - 1][16][64];
-        if (wib > 0)
+    __shared__ float part[2][16][64];
+    if (wib > 0)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) part[wib - 1][j][lane] = acc[j];
-        __syncthreads();
-        if (wib > 0) return;
+        for (int j = 0; j < 16; ++j) part[wib - 1][j][lane] = acc[j];
+    __syncthreads();
+    if (wib > 0) return;
 #pragma unroll
-        for (int s = 0; s < SPLIT - 1; ++s)
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[j] += part[s][j][lane];
-    }
+        for (int j = 0; j < 16; ++j) acc[j] += part[s][j][lane];
     const size_t o = (((size_t)b * kNetG + y) * kNetG + x0) * kNetC;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         const int row = 8 * (j / 4) + 4 * hk + (j % 4);  // pixel within the tile
         const __bf16 hi = (__bf16)acc[j];
         out[o + (size_t)row * kNetC + r] = hi;
-        if (out_lo) out_lo[o + (size_t)row * kNetC + r] = (__bf16)(acc[j] - (float)hi);
+        out_lo[o + (size_t)row * kNetC + r] = (__bf16)(acc[j] - (float)hi);
     }
 }
 
-template __global__ void k_conv32<1>(const __bf16 *, const __bf16 *, const __bf16 *, const __bf16 *, __bf16 *,
-                                      __bf16 *, int, int);
-template __global__ void k_conv32<3>(const __bf16 *, const __bf16 *, const __bf16 *, const __bf16 *, __bf16 *,
-                                      __bf16 *, int, int);
+// Larger batches.  Reading every tap of every 32-pixel tile through the L1, and
+// the layer's 36 KB of weights again for each tile, is what bounds such a
+// product (72 KB of L1 reads for 54 MFMAs), so here a wavefront keeps all the
+// weights in registers (36 fragments, 144 registers) and a workgroup of four
+// (one 32-pixel tile each) walks rows of the image that are `dil` apart: the
+// three rows an output row needs lie in a ring of four in LDS, each read from
+// memory once per walk, the next one on its way during this row's products.
+// A row's 16-byte chunks are swizzled (chunk c of pixel x at place
+// c ^ (x / 4) % 4), so that any 16 consecutive pixels' chunks lie in 16
+// different bank groups.  The weights are the MFMA's first operand, so a lane
+// ends with channels of one pixel and, after one swap between the wave's
+// halves, writes them as 16-byte stores.
+// PAIR: activations and weights are (hi, lo) pairs; else single BF16.
+// Walks of `seg` rows: workgroup = (image, row class y % dil, segment).
+// Measured, 64 images in pairs: 206 -> 64 us a layer (4.2 TB/s of the 268 MB it
+// reads and writes, 0.9 PFLOP/s of MFMAs); a training step of 32 images, whose
+// eight launches averaged 67.5 us: 36 us forward, 16 us for a gradient.
+namespace {
+constexpr int kRowBytes = kNetG * kNetC * 2;  // one row of one plane: 8 KB
+__device__ __forceinline__ unsigned pack2(__bf16 a, __bf16 b) {
+    return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+}
+// registers j = 0 .. 15 of a tile as BF16: 16 bytes at channel 8 hk and 16 at
+// channel 16 + 8 hk of this lane's pixel
+__device__ __forceinline__ void store_pixel(__bf16 *px, int hk, const __bf16 (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const auto s0 = __builtin_amdgcn_permlane32_swap(pack2(v[8 * q], v[8 * q + 1]), pack2(v[8 * q + 4], v[8 * q + 5]),
+                                                         false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(pack2(v[8 * q + 2], v[8 * q + 3]),
+                                                         pack2(v[8 * q + 6], v[8 * q + 7]), false, false);
+        uint4 o;
+        o.x = s0[0];
+        o.y = s1[0];
+        o.z = s0[1];
+        o.w = s1[1];
+        *reinterpret_cast<uint4 *>(px + 16 * q + 8 * hk) = o;
+    }
+}
+}  // namespace
+
+template <bool PAIR>
+__global__ __launch_bounds__(256, 2) void k_conv32(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
+                                                   const __bf16 *__restrict__ w, const __bf16 *__restrict__ w_lo,
+                                                   __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int dil,
+                                                   int seg) {
+    constexpr int PL = PAIR ? 2 : 1;  // planes
+    __shared__ __attribute__((aligned(16))) unsigned char lds[4][PL][kRowBytes];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wib = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chain = kNetG / dil, segs = chain / seg;
+    int q = xcd_block();
+    const int i0 = (q % segs) * seg;
+    q /= segs;
+    const int y0 = q % dil, b = q / dil;
+    const size_t img = (size_t)b * kNetG * kNetG * kNetC;
+    const int r = lane & 31, hk = lane >> 5, x0 = 32 * wib;
+    auto row_y = [&](int i) { return y0 + dil * ((i0 + i) & (chain - 1)); };  // row i of the walk (i >= -1)
+
+    bf16x8 wf[9][2], wl[PAIR ? 9 : 1][2];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int wo = (r * 9 + t) * kNetC + 16 * h + 8 * hk;
+            wf[t][h] = load8(w + wo);
+            if constexpr (PAIR) wl[t][h] = load8(w_lo + wo);
+        }
+    // a row: 512 chunks of 16 bytes a plane, two per thread, to their swizzled places
+    bf16x8 st[PL][2];
+    auto fetch = [&](int i) {
+        const size_t o = img + (size_t)row_y(i) * kNetG * kNetC;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            st[0][k] = load8(in + o + 8 * (tid + 256 * k));
+            if constexpr (PAIR) st[1][k] = load8(in_lo + o + 8 * (tid + 256 * k));
+        }
+    };
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int c = tid + 256 * k, x = c >> 2;
+                *reinterpret_cast<bf16x8 *>(&lds[slot][p][64 * x + 16 * ((c ^ (x >> 2)) & 3)]) = st[p][k];
+            }
+    };
+#pragma unroll
+    for (int i = -1; i < 2; ++i) {
+        fetch(i);
+        put(i + 1);
+    }
+    // byte places of this lane's chunk (channels 16 h + 8 hk ..) for the three column shifts
+    int at[3][2];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+        const int x = wrapg(x0 + r + (kx - 1) * dil);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) at[kx][h] = 64 * x + 16 * ((2 * h + hk) ^ ((x >> 2) & 3));
+    }
+    __syncthreads();
+    for (int i = 0; i < seg; ++i) {
+        if (i + 1 < seg) fetch(i + 2);
+        f32x16 acc = {};
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const unsigned char *row = lds[(i + t / 3) & 3][0];  // walk row i - 1 + t / 3
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned char *p = row + at[t % 3][h];
+                const bf16x8 av = *reinterpret_cast<const bf16x8 *>(p);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t][h], av, acc, 0, 0, 0);
+                if constexpr (PAIR) {
+                    const bf16x8 al = *reinterpret_cast<const bf16x8 *>(p + kRowBytes);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t][h], al, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl[t][h], av, acc, 0, 0, 0);
+                }
+            }
+        }
+        const size_t o = img + ((size_t)row_y(i) * kNetG + x0 + r) * kNetC;
+        __bf16 hi[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) hi[j] = (__bf16)acc[j];
+        store_pixel(out + o, hk, hi);
+        if constexpr (PAIR) {
+            __bf16 lo[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) lo[j] = (__bf16)(acc[j] - (float)hi[j]);
+            store_pixel(out_lo + o, hk, lo);
+        }
+        // the slot of walk row i - 2, last read two rows ago
+        if (i + 1 < seg) put((i + 3) & 3);
+        __syncthreads();
+    }
+}
+
+template __global__ void k_conv32<true>(const __bf16 *, const __bf16 *, const __bf16 *, const __bf16 *, __bf16 *,
+                                        __bf16 *, int, int);
+template __global__ void k_conv32<false>(const __bf16 *, const __bf16 *, const __bf16 *, const __bf16 *, __bf16 *,
+                                         __bf16 *, int, int);
 
 // Weight gradient of a 32 -> 32 layer:
 //   dw[co][tap][ci] = sum_{b, y, x} g[b][y][x][co] * in[b][y + dy][x + dx][ci]
