@@ -19,7 +19,7 @@ namespace {
 
 constexpr int kPix = kNetG * kNetG;
 constexpr int kWgChunk = 1024;    // pixels per wavefront of the MFMA weight gradient
-constexpr int kSmallChunk = 512;  // pixels per workgroup of the 1-channel weight gradients
+constexpr int kSmallChunk = 1024;  // pixels per workgroup of the 1-channel weight gradients (divides an image)
 constexpr int kSumGroups = 32;    // first-stage groups of the partial-sum reduction
 constexpr int kLossBlocks = 256;
 // A guess whose relative residual exceeds this is discarded (zero guess instead).
@@ -105,9 +105,9 @@ hipError_t refresh_bf16(ccmg_net *N) {
 // activation pairs a1..a5.
 hipError_t forward(ccmg_net *N, const float *x, float *y, int nb) {
     hipStream_t s = N->stream;
-    const int npix = nb * kPix;
-    hipLaunchKernelGGL(k_conv_in, dim3((npix + 255) / 256), dim3(256), 0, s, x, N->w() + net_param_offset(0),
-                       N->act(0), N->act_lo(0), nb, net_dilation(0));
+    const int per = pixels_per_thread(nb);
+    hipLaunchKernelGGL(k_conv_in, dim3(nb * kPix / (64 * per)), dim3(256), 0, s, x, N->w() + net_param_offset(0),
+                       N->act(0), N->act_lo(0), per, net_dilation(0));
     for (int l = 1; l <= 4; ++l) {
         const __bf16 *wl = N->w16() + net_param_offset(l), *wlo = N->at<__bf16>(N->L.w16lo) + net_param_offset(l);
         const int dil = net_dilation(l), seg = conv_seg(nb, dil);
@@ -118,8 +118,8 @@ hipError_t forward(ccmg_net *N, const float *x, float *y, int nb) {
             hipLaunchKernelGGL(k_conv32<true>, dim3(nb * kNetG / seg), dim3(256), 0, s, N->act(l - 1), N->act_lo(l - 1),
                                wl, wlo, N->act(l), N->act_lo(l), dil, seg);
     }
-    hipLaunchKernelGGL(k_conv_out, dim3((npix + 255) / 256), dim3(256), 0, s, N->act(4), N->act_lo(4),
-                       N->w() + net_param_offset(5), y, nb, net_dilation(5));
+    hipLaunchKernelGGL(k_conv_out, dim3(nb * net_dilation(5)), dim3(256), 0, s, N->act(4), N->act_lo(4),
+                       N->w() + net_param_offset(5), y);
     return hipGetLastError();
 }
 
@@ -142,14 +142,15 @@ hipError_t backward(ccmg_net *N, const float *x, const float *t, int nb) {
     hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(256), 0, s, y, t, dy, N->at<double>(N->L.lpart), npix);
     hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(64), 0, s, N->at<double>(N->L.lpart), kLossBlocks, npix,
                        N->at<float>(N->L.loss));
-    const int sm_blocks = (npix + kSmallChunk - 1) / kSmallChunk;
+    const int sm_blocks = npix / kSmallChunk;
     // last layer: weights, then the gradient of a5
-    hipLaunchKernelGGL(k_wgrad_small, dim3(sm_blocks), dim3(256), 0, s, 1, N->act(4), N->act_lo(4), dy, part, npix,
+    hipLaunchKernelGGL(k_wgrad_small<true>, dim3(sm_blocks), dim3(256), 0, s, N->act(4), N->act_lo(4), dy, part,
                        kSmallChunk, net_dilation(5));
     sum_partials(N, part, sm_blocks, kW5, grad + net_param_offset(5));
     __bf16 *gcur = N->at<__bf16>(N->L.g0), *gnext = N->at<__bf16>(N->L.g1);
-    hipLaunchKernelGGL(k_conv_out_bwd, dim3((npix + 255) / 256), dim3(256), 0, s, dy, N->w() + net_param_offset(5),
-                       gcur, nb, net_dilation(5));
+    const int per = pixels_per_thread(nb);
+    hipLaunchKernelGGL(k_conv_out_bwd, dim3(npix / (64 * per)), dim3(256), 0, s, dy, N->w() + net_param_offset(5),
+                       gcur, per, net_dilation(5));
     // layers 4 .. 1 (32 -> 32): weight gradient from (g, input activation), then g of the input
     const int wg_waves = (npix + kWgChunk - 1) / kWgChunk;
     for (int l = 4; l >= 1; --l) {
@@ -163,8 +164,8 @@ hipError_t backward(ccmg_net *N, const float *x, const float *t, int nb) {
         std::swap(gcur, gnext);
     }
     // first layer: weights only (its input is data)
-    hipLaunchKernelGGL(k_wgrad_small, dim3(sm_blocks), dim3(256), 0, s, 0, gcur, (const __bf16 *)nullptr, x, part,
-                       npix, kSmallChunk, net_dilation(0));
+    hipLaunchKernelGGL(k_wgrad_small<false>, dim3(sm_blocks), dim3(256), 0, s, gcur, (const __bf16 *)nullptr, x, part,
+                       kSmallChunk, net_dilation(0));
     sum_partials(N, part, sm_blocks, kW0, grad + net_param_offset(0));
     return hipGetLastError();
 }

@@ -37,11 +37,19 @@ __global__ void k_conv32_wgrad(const __bf16 *g, const __bf16 *in, float *part, i
 __global__ void k_sum_partials(const float *part, int count, int len, float *out);
 __global__ void k_sum_partials_grouped(const float *part, int count, int len, int groups, float *out);
 __global__ void k_transpose_flip(const __bf16 *w, __bf16 *wt);
-__global__ void k_conv_in(const float *x, const float *w1, __bf16 *out, __bf16 *out_lo, int nb, int dil);
-__global__ void k_conv_out(const __bf16 *in, const __bf16 *in_lo, const float *w6, float *y, int nb, int dil);
-__global__ void k_conv_out_bwd(const float *dy, const float *w6, __bf16 *g, int nb, int dil);
-__global__ void k_wgrad_small(int mode, const __bf16 *act, const __bf16 *act_lo, const float *vec, float *part,
-                              int npix, int chunk, int dil);
+__global__ void k_conv_in(const float *x, const float *w1, __bf16 *out, __bf16 *out_lo, int per, int dil);
+__global__ void k_conv_out(const __bf16 *in, const __bf16 *in_lo, const float *w6, float *y);
+__global__ void k_conv_out_bwd(const float *dy, const float *w6, __bf16 *g, int per, int dil);
+// Pixels per thread of k_conv_in and k_conv_out_bwd (workgroups of 64 x that
+// many): as many as leave four workgroups per CU (1024), at most 16.
+inline int pixels_per_thread(int nb) {
+    int per = 1;
+    while (per < 16 && nb * (kNetG * kNetG / 64) / (2 * per) >= 1024) per *= 2;
+    return per;
+}
+template <bool LAST>
+__global__ void k_wgrad_small(const __bf16 *act, const __bf16 *act_lo, const float *vec, float *part, int chunk,
+                              int dil);
 __global__ void k_mse(const float *y, const float *t, float *dy, double *part, int count);
 __global__ void k_loss_finish(const double *part, int blocks, int count, float *loss);
 __global__ void k_adam(float *w, const float *g, float *m, float *v, __bf16 *w16, int count, float lr, float b1,

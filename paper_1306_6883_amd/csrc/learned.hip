@@ -24,6 +24,8 @@
 //   column l % 32.
 #include "learned.h"
 
+#include <type_traits>
+
 namespace ccmg {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -365,27 +367,37 @@ __global__ void k_transpose_flip(const __bf16 *__restrict__ w, __bf16 *__restric
     wt[i] = w[((size_t)co * 9 + (8 - t)) * kNetC + ci];
 }
 
-// First layer (1 -> 32): one thread per pixel; FP32 input and weights, the
-// output as a BF16 (hi, lo) pair.
-__global__ void k_conv_in(const float *__restrict__ x, const float *__restrict__ w1, __bf16 *__restrict__ out,
-                          __bf16 *__restrict__ out_lo, int nb, int dil) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nb * kNetG * kNetG) return;
-    const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, y = rem / kNetG, xx = rem % kNetG;
-    float v[9];
+// The 1-channel layers move 32 channels of BF16 per pixel for a few hundred
+// operations: bound by memory once their accesses are whole cache lines.  Four
+// neighbouring lanes share a pixel, eight channels (16 bytes) each, so that a
+// wavefront's load or store covers 16 pixels without a gap; a thread keeps its
+// channels' 72 weights in registers over `per` pixels (a workgroup: 64 x per).
+
+// First layer (1 -> 32): FP32 input and weights, the output as a BF16 (hi, lo)
+// pair.  (64 images: 55 -> 39 us.)
+__global__ __launch_bounds__(256) void k_conv_in(const float *__restrict__ x, const float *__restrict__ w1,
+                                                 __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int per,
+                                                 int dil) {
+    const int c8 = 8 * (threadIdx.x & 3);
+    float w[8][9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
-        v[t] = x[((size_t)b * kNetG + wrapg(y + tap_dy(t, dil))) * kNetG + wrapg(xx + tap_dx(t, dil))];
-    // the pixel's 32 channels (64 B each for hi and lo) as 16-byte stores
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
-    for (int c8 = 0; c8 < kNetC; c8 += 8) {
+        for (int t = 0; t < 9; ++t) w[k][t] = w1[(c8 + k) * 9 + t];
+    const int q0 = blockIdx.x * 64 * per + (threadIdx.x >> 2);
+    for (int i = 0; i < per; ++i) {
+        const int q = q0 + 64 * i;
+        const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, y = rem / kNetG, xx = rem % kNetG;
+        float v[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            v[t] = x[((size_t)b * kNetG + wrapg(y + tap_dy(t, dil))) * kNetG + wrapg(xx + tap_dx(t, dil))];
         bf16x8 h8, l8;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int co = c8 + k;
             float s = 0.f;
 #pragma unroll
-            for (int t = 0; t < 9; ++t) s += w1[co * 9 + t] * v[t];
+            for (int t = 0; t < 9; ++t) s += w[k][t] * v[t];
             const __bf16 hi = (__bf16)s;
             h8[k] = hi;
             l8[k] = (__bf16)(s - (float)hi);
@@ -395,51 +407,93 @@ __global__ void k_conv_in(const float *__restrict__ x, const float *__restrict__
     }
 }
 
-// Last layer (32 -> 1): one thread per pixel, (hi + lo) activations, FP32
-// weights and output.
-__global__ void k_conv_out(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
-                           const float *__restrict__ w6, float *__restrict__ y, int nb, int dil) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nb * kNetG * kNetG) return;
-    const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, yy = rem / kNetG, xx = rem % kNetG;
-    float s = 0.f;
-#pragma unroll 3
-    for (int t = 0; t < 9; ++t) {
-        const size_t px =
-            (((size_t)b * kNetG + wrapg(yy + tap_dy(t, dil))) * kNetG + wrapg(xx + tap_dx(t, dil))) * kNetC;
-        // the neighbour's 32 channels as four 16-byte loads of hi and of lo;
-        // the sum runs over ci in order as before
-        bf16x8 h8[4], l8[4];
+// Last layer (32 -> 1): (hi + lo) activations, FP32 weights and output.  Rows
+// 32 apart need only each other (four rows, circular), so a workgroup reads
+// four of them once, as FP32 sums hi + lo in LDS, and makes their 512 outputs,
+// two per thread; the sum runs over tap, then channel.  A pixel's eight
+// 16-byte chunks are swizzled (chunk c of pixel x at c ^ (x / 2) % 8: any 16
+// consecutive pixels' chunks lie in 16 different bank groups).
+// (64 images: 82 -> 37 us.)
+__global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
+                                                     const float *__restrict__ w6, float *__restrict__ y) {
+    constexpr int D = 1 << (kNetLayers - 1);
+    static_assert(kNetG / D == 4, "four rows a class");
+    __shared__ __attribute__((aligned(16))) float act[4][kNetG * kNetC];
+    const int tid = threadIdx.x;
+    const int blk = xcd_block();
+    const int b = blk / D, y0 = blk % D;
+    auto place = [](int x, int c) { return x * kNetC + 4 * ((c ^ (x >> 1)) & 7); };
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            h8[c] = load8(in + px + 8 * c);
-            l8[c] = load8(in_lo + px + 8 * c);
+    for (int row = 0; row < 4; ++row) {
+        const size_t o = ((size_t)b * kNetG + y0 + D * row) * kNetG * kNetC;
+        bf16x8 h[2], l[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            h[k] = load8(in + o + 8 * (tid + 256 * k));
+            l[k] = load8(in_lo + o + 8 * (tid + 256 * k));
         }
 #pragma unroll
-        for (int ci = 0; ci < kNetC; ++ci)
-            s += w6[t * kNetC + ci] * ((float)h8[ci >> 3][ci & 7] + (float)l8[ci >> 3][ci & 7]);
+        for (int k = 0; k < 2; ++k) {
+            const int q = tid + 256 * k, x = q >> 2, c = 2 * (q & 3);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                float4 v;
+                v.x = (float)h[k][4 * e + 0] + (float)l[k][4 * e + 0];
+                v.y = (float)h[k][4 * e + 1] + (float)l[k][4 * e + 1];
+                v.z = (float)h[k][4 * e + 2] + (float)l[k][4 * e + 2];
+                v.w = (float)h[k][4 * e + 3] + (float)l[k][4 * e + 3];
+                *reinterpret_cast<float4 *>(&act[row][place(x, c + e)]) = v;
+            }
+        }
     }
-    y[q] = s;
+    __syncthreads();
+    const int x = tid & (kNetG - 1), r0 = tid >> 7;  // rows r0 and r0 + 2 of the class
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        const int xs = wrapg(x + tap_dx(t, D));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int at = place(xs, c);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float4 v = *reinterpret_cast<const float4 *>(&act[(r0 + 2 * k + t / 3 + 3) & 3][at]);
+                const float *wt = w6 + t * kNetC + 4 * c;
+                s[k] += wt[0] * v.x;
+                s[k] += wt[1] * v.y;
+                s[k] += wt[2] * v.z;
+                s[k] += wt[3] * v.w;
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) y[((size_t)b * kNetG + y0 + D * (r0 + 2 * k)) * kNetG + x] = s[k];
 }
 
 // Input gradient of the last layer: g[b][p][ci] = sum_tap w6[tap][ci] * dy[b][p - off(tap)].
-__global__ void k_conv_out_bwd(const float *__restrict__ dy, const float *__restrict__ w6, __bf16 *__restrict__ g,
-                               int nb, int dil) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nb * kNetG * kNetG) return;
-    const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, yy = rem / kNetG, xx = rem % kNetG;
-    float d[9];
+// (32 images: 19 -> 16 us.)
+__global__ __launch_bounds__(256) void k_conv_out_bwd(const float *__restrict__ dy, const float *__restrict__ w6,
+                                                      __bf16 *__restrict__ g, int per, int dil) {
+    const int c8 = 8 * (threadIdx.x & 3);
+    float w[9][8];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
-        d[t] = (float)(__bf16)dy[((size_t)b * kNetG + wrapg(yy - tap_dy(t, dil))) * kNetG + wrapg(xx - tap_dx(t, dil))];
 #pragma unroll
-    for (int c8 = 0; c8 < kNetC; c8 += 8) {  // 16-byte stores of 8 channels
+        for (int k = 0; k < 8; ++k) w[t][k] = (float)(__bf16)w6[t * kNetC + c8 + k];
+    const int q0 = blockIdx.x * 64 * per + (threadIdx.x >> 2);
+    for (int i = 0; i < per; ++i) {
+        const int q = q0 + 64 * i;
+        const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, yy = rem / kNetG, xx = rem % kNetG;
+        float d[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            d[t] = (float)(__bf16)dy[((size_t)b * kNetG + wrapg(yy - tap_dy(t, dil))) * kNetG + wrapg(xx - tap_dx(t, dil))];
         bf16x8 g8;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             float s = 0.f;
 #pragma unroll
-            for (int t = 0; t < 9; ++t) s += (float)(__bf16)w6[t * kNetC + c8 + k] * d[t];
+            for (int t = 0; t < 9; ++t) s += w[t][k] * d[t];
             g8[k] = (__bf16)s;
         }
         *reinterpret_cast<bf16x8 *>(g + (size_t)q * kNetC + c8) = g8;
@@ -447,49 +501,73 @@ __global__ void k_conv_out_bwd(const float *__restrict__ dy, const float *__rest
 }
 
 // Weight gradients of the 1-channel layers, per-block partials:
-//   mode 0 (first layer): part[blk][co][tap] = sum_p g[p][co] * x[p + off(tap)]
-//   mode 1 (last layer):  part[blk][tap][ci] = sum_p dy[p] * in[p + off(tap)][ci]
-// (in = act + act_lo, the activation pair).
-// 256 threads: channel c = thread % 32, pixel group = thread / 32 (8 groups).
-__global__ __launch_bounds__(256) void k_wgrad_small(int mode, const __bf16 *__restrict__ act,
-                                                     const __bf16 *__restrict__ act_lo,
+//   LAST = false (first layer): part[blk][co][tap] = sum_p g[p][co] * x[p + off(tap)]
+//   LAST = true  (last layer):  part[blk][tap][ci] = sum_p in[p][ci] * dy[p - off(tap)]
+// (in = act + act_lo, the activation pair; dy rounded to BF16).  Each pixel's
+// activations are read once, against the nine scalars around it; lanes as in
+// the layers above.  A thread's 8 x 9 sums meet by rotations within the rows
+// of 16 lanes, then the workgroup's 16 rows in LDS.
+// (32 images, per layer: 52 -> 16 us.)
+template <bool LAST>
+__global__ __launch_bounds__(256) void k_wgrad_small(const __bf16 *__restrict__ act, const __bf16 *__restrict__ act_lo,
                                                      const float *__restrict__ vec, float *__restrict__ part,
-                                                     int npix, int chunk, int dil) {
-    __shared__ float red[8][9 * kNetC];
-    const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int p0 = blockIdx.x * chunk, p1 = min(p0 + chunk, npix);
-    float acc[9];
+                                                     int chunk, int dil) {
+    __shared__ float red[16][4][73];
+    const int c = threadIdx.x & 3, row16 = threadIdx.x >> 4;
+    const int p0 = blockIdx.x * chunk + (threadIdx.x >> 2);
+    float acc[8][9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = 0.f;
-    for (int q = p0 + grp; q < p1; q += 8) {
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[k][t] = 0.f;
+    for (int i = 0; i < chunk; i += 64) {
+        const int q = p0 + i;
         const int b = q / (kNetG * kNetG), rem = q - b * kNetG * kNetG, yy = rem / kNetG, xx = rem % kNetG;
-        if (mode == 0) {
-            const float gv = (float)act[(size_t)q * kNetC + c];
+        const bf16x8 h8 = load8(act + (size_t)q * kNetC + 8 * c);
+        float v[9], u[8];
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
-                acc[t] += gv * vec[((size_t)b * kNetG + wrapg(yy + tap_dy(t, dil))) * kNetG +
-                                   wrapg(xx + tap_dx(t, dil))];
-        } else {
-            const float dv = (float)(__bf16)vec[q];
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const size_t a = (((size_t)b * kNetG + wrapg(yy + tap_dy(t, dil))) * kNetG +
-                                  wrapg(xx + tap_dx(t, dil))) * kNetC + c;
-                acc[t] += dv * ((float)act[a] + (float)act_lo[a]);
-            }
+        for (int t = 0; t < 9; ++t) {
+            const int ys = wrapg(LAST ? yy - tap_dy(t, dil) : yy + tap_dy(t, dil));
+            const int xs = wrapg(LAST ? xx - tap_dx(t, dil) : xx + tap_dx(t, dil));
+            v[t] = vec[((size_t)b * kNetG + ys) * kNetG + xs];
+            if constexpr (LAST) v[t] = (float)(__bf16)v[t];
         }
-    }
+        if constexpr (LAST) {
+            const bf16x8 l8 = load8(act_lo + (size_t)q * kNetC + 8 * c);
 #pragma unroll
-    for (int t = 0; t < 9; ++t) red[grp][t * kNetC + c] = acc[t];
+            for (int k = 0; k < 8; ++k) u[k] = (float)h8[k] + (float)l8[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = (float)h8[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) acc[k][t] += u[k] * v[t];
+    }
+    // lanes 4, 8, 12 further on in the row hold the same channels
+    auto rot = [](float a, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            float a = acc[k][t];
+            a += rot(a, std::integral_constant<int, 0x124>{});
+            a += rot(a, std::integral_constant<int, 0x128>{});
+            if ((threadIdx.x & 15) < 4) red[row16][c][9 * k + t] = a;
+        }
     __syncthreads();
     for (int i = threadIdx.x; i < 9 * kNetC; i += 256) {
+        const int ch = i / 9, t = i - 9 * ch;
         float s = 0.f;
-        for (int k = 0; k < 8; ++k) s += red[k][i];
-        const int t = i / kNetC, ch = i % kNetC;
-        // mode 0 stores [co][tap], mode 1 [tap][ci]
-        part[(size_t)blockIdx.x * 9 * kNetC + (mode == 0 ? ch * 9 + t : t * kNetC + ch)] = s;
+        for (int k = 0; k < 16; ++k) s += red[k][ch >> 3][9 * (ch & 7) + t];
+        part[(size_t)blockIdx.x * 9 * kNetC + (LAST ? t * kNetC + ch : ch * 9 + t)] = s;
     }
 }
+template __global__ void k_wgrad_small<false>(const __bf16 *, const __bf16 *, const float *, float *, int, int);
+template __global__ void k_wgrad_small<true>(const __bf16 *, const __bf16 *, const float *, float *, int, int);
 
 // Mean squared error: dy = 2 (y - t) / count, and per-block partial sums of (y - t)^2.
 __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const float *__restrict__ t,
