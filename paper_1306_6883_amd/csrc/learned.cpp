@@ -18,10 +18,7 @@ using namespace ccmg;
 namespace {
 
 constexpr int kPix = kNetG * kNetG;
-constexpr int kWgChunk = 1024;    // pixels per wavefront of the MFMA weight gradient
 constexpr int kSmallChunk = 1024;  // pixels per workgroup of the 1-channel weight gradients (divides an image)
-constexpr int kSumGroups = 32;    // first-stage groups of the partial-sum reduction
-constexpr int kLossBlocks = 256;
 // A guess whose relative residual exceeds this is discarded (zero guess instead).
 constexpr double kGuessReject = 1e6;
 
@@ -53,10 +50,8 @@ NetLayout net_layout(int batch, int nmax) {
     L.g1 = take(2 * npix * kNetC);
     L.y = take(sizeof(float) * npix);
     L.dy = take(sizeof(float) * npix);
-    const size_t wg_waves = (npix + kWgChunk - 1) / kWgChunk;
-    const size_t sm_blocks = (npix + kSmallChunk - 1) / kSmallChunk;
-    L.part = take(sizeof(float) * std::max(wg_waves * kWmid, sm_blocks * kW0));
-    L.part2 = take(sizeof(float) * kSumGroups * kWmid);
+    L.part = take(sizeof(float) * std::max((size_t)wgrad_blocks_max(batch) * kWmid, npix / kSmallChunk * kW0));
+    L.part2 = take(sizeof(float) * kSumGroups * kNetParams);
     L.lpart = take(sizeof(double) * kLossBlocks);
     L.loss = take(sizeof(float) * 4);
     L.x1 = take(sizeof(float) * kPix);
@@ -94,10 +89,7 @@ int hs(hipError_t e) { return e == hipSuccess ? CCMG_OK : CCMG_EHIP; }
 
 hipError_t refresh_bf16(ccmg_net *N) {
     hipLaunchKernelGGL(k_to_bf16, dim3((kNetParams + 255) / 256), dim3(256), 0, N->stream, N->w(), N->w16(),
-                       N->at<__bf16>(N->L.w16lo), kNetParams);
-    for (int l = 1; l <= 4; ++l)
-        hipLaunchKernelGGL(k_transpose_flip, dim3((kWmid + 255) / 256), dim3(256), 0, N->stream,
-                           N->w16() + net_param_offset(l), N->at<__bf16>(N->L.wt16) + (size_t)(l - 1) * kWmid);
+                       N->at<__bf16>(N->L.w16lo), N->at<__bf16>(N->L.wt16), kNetParams);
     return hipGetLastError();
 }
 
@@ -123,41 +115,36 @@ hipError_t forward(ccmg_net *N, const float *x, float *y, int nb) {
     return hipGetLastError();
 }
 
-// out[len] = sum of `count` partial vectors, in a fixed order (two stages).
-void sum_partials(ccmg_net *N, const float *part, int count, int len, float *out) {
-    const int groups = std::min(count, kSumGroups);
-    float *p2 = N->at<float>(N->L.part2);
-    hipLaunchKernelGGL(k_sum_partials_grouped, dim3((len + 255) / 256, groups), dim3(256), 0, N->stream, part, count,
-                       len, groups, p2);
-    hipLaunchKernelGGL(k_sum_partials, dim3((len + 255) / 256), dim3(256), 0, N->stream, p2, groups, len, out);
+// First stage of a layer's gradient (see k_sum_partials): `count` partial
+// vectors of length len into the groups' sums at the layer's place.
+void sum_partials(ccmg_net *N, const float *part, int count, int len, int layer) {
+    hipLaunchKernelGGL(k_sum_partials, dim3((len + 255) / 256, kSumGroups), dim3(256), 0, N->stream, part, count, len,
+                       N->at<float>(N->L.part2) + net_param_offset(layer));
 }
 
-// Loss and gradients of all parameters into N->grad (after forward() on x).
+// Backward through every layer (after forward() on x): the gradients as groups'
+// sums, for finish().
 hipError_t backward(ccmg_net *N, const float *x, const float *t, int nb) {
     hipStream_t s = N->stream;
     const int npix = nb * kPix;
-    float *grad = N->at<float>(N->L.grad);
     float *part = N->at<float>(N->L.part);
     float *y = N->at<float>(N->L.y), *dy = N->at<float>(N->L.dy);
     hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(256), 0, s, y, t, dy, N->at<double>(N->L.lpart), npix);
-    hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(64), 0, s, N->at<double>(N->L.lpart), kLossBlocks, npix,
-                       N->at<float>(N->L.loss));
     const int sm_blocks = npix / kSmallChunk;
     // last layer: weights, then the gradient of a5
     hipLaunchKernelGGL(k_wgrad_small<true>, dim3(sm_blocks), dim3(256), 0, s, N->act(4), N->act_lo(4), dy, part,
                        kSmallChunk, net_dilation(5));
-    sum_partials(N, part, sm_blocks, kW5, grad + net_param_offset(5));
+    sum_partials(N, part, sm_blocks, kW5, 5);
     __bf16 *gcur = N->at<__bf16>(N->L.g0), *gnext = N->at<__bf16>(N->L.g1);
     const int per = pixels_per_thread(nb);
     hipLaunchKernelGGL(k_conv_out_bwd, dim3(npix / (64 * per)), dim3(256), 0, s, dy, N->w() + net_param_offset(5),
                        gcur, per, net_dilation(5));
     // layers 4 .. 1 (32 -> 32): weight gradient from (g, input activation), then g of the input
-    const int wg_waves = (npix + kWgChunk - 1) / kWgChunk;
     for (int l = 4; l >= 1; --l) {
-        hipLaunchKernelGGL(k_conv32_wgrad, dim3((3 * wg_waves + 3) / 4), dim3(256), 0, s, gcur, N->act(l - 1), part, npix,
-                           kWgChunk, net_dilation(l));
-        sum_partials(N, part, wg_waves, kWmid, grad + net_param_offset(l));
-        const int dil = net_dilation(l), seg = conv_seg(nb, dil);
+        const int dil = net_dilation(l), seg = conv_seg(nb, dil), blocks = wgrad_blocks(nb, dil);
+        auto *wgrad = dil >= 8 ? k_conv32_wgrad<16> : dil == 4 ? k_conv32_wgrad<8> : k_conv32_wgrad<4>;
+        hipLaunchKernelGGL(wgrad, dim3(blocks), dim3(256), 0, s, gcur, N->act(l - 1), part, dil, seg);
+        sum_partials(N, part, blocks, kWmid, l);
         hipLaunchKernelGGL(k_conv32<false>, dim3(nb * kNetG / seg), dim3(256), 0, s, gcur, (const __bf16 *)nullptr,
                            N->at<__bf16>(N->L.wt16) + (size_t)(l - 1) * kWmid, (const __bf16 *)nullptr, gnext,
                            (__bf16 *)nullptr, dil, seg);
@@ -166,7 +153,19 @@ hipError_t backward(ccmg_net *N, const float *x, const float *t, int nb) {
     // first layer: weights only (its input is data)
     hipLaunchKernelGGL(k_wgrad_small<false>, dim3(sm_blocks), dim3(256), 0, s, gcur, (const __bf16 *)nullptr, x, part,
                        kSmallChunk, net_dilation(0));
-    sum_partials(N, part, sm_blocks, kW0, grad + net_param_offset(0));
+    sum_partials(N, part, sm_blocks, kW0, 0);
+    return hipGetLastError();
+}
+
+// Loss and gradient of all parameters into N->grad; with lr > 0 also Adam's
+// step (N->step already counts it).
+hipError_t finish(ccmg_net *N, int nb, float lr) {
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float c1 = 1.f - std::pow(b1, (float)N->step), c2 = 1.f - std::pow(b2, (float)N->step);
+    hipLaunchKernelGGL(lr > 0.f ? k_finish<true> : k_finish<false>, dim3((kNetParams + 255) / 256), dim3(256), 0,
+                       N->stream, N->at<float>(N->L.part2), N->at<float>(N->L.grad), N->at<double>(N->L.lpart),
+                       nb * kPix, N->at<float>(N->L.loss), N->w(), N->at<float>(N->L.m), N->at<float>(N->L.v),
+                       N->w16(), N->at<__bf16>(N->L.w16lo), N->at<__bf16>(N->L.wt16), lr, b1, b2, eps, c1, c2);
     return hipGetLastError();
 }
 
@@ -263,6 +262,7 @@ int ccmg_net_loss_grad(ccmg_net *N, const float *d_x, const float *d_t, int nb, 
     if (!N || !d_x || !d_t || nb < 1 || nb > N->batch) return CCMG_EINVAL;
     hipError_t e = forward(N, d_x, N->at<float>(N->L.y), nb);
     if (e == hipSuccess) e = backward(N, d_x, d_t, nb);
+    if (e == hipSuccess) e = finish(N, nb, 0.f);
     if (e == hipSuccess && d_grad)
         e = hipMemcpyAsync(d_grad, N->at<float>(N->L.grad), sizeof(float) * kNetParams, hipMemcpyDeviceToDevice,
                            N->stream);
@@ -274,16 +274,11 @@ int ccmg_net_loss_grad(ccmg_net *N, const float *d_x, const float *d_t, int nb, 
 
 int ccmg_net_train_step(ccmg_net *N, const float *d_x, const float *d_t, int nb, float lr, float *loss) {
     if (!N || !d_x || !d_t || nb < 1 || nb > N->batch || !(lr > 0)) return CCMG_EINVAL;
-    int st = ccmg_net_loss_grad(N, d_x, d_t, nb, nullptr, nullptr);
-    if (st != CCMG_OK) return st;
+    hipError_t e = forward(N, d_x, N->at<float>(N->L.y), nb);
+    if (e == hipSuccess) e = backward(N, d_x, d_t, nb);
+    if (e != hipSuccess) return hs(e);
     N->step += 1;
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.f - std::pow(b1, (float)N->step), c2 = 1.f - std::pow(b2, (float)N->step);
-    hipLaunchKernelGGL(k_adam, dim3((kNetParams + 255) / 256), dim3(256), 0, N->stream, N->w(),
-                       N->at<float>(N->L.grad), N->at<float>(N->L.m), N->at<float>(N->L.v), N->w16(), kNetParams, lr,
-                       b1, b2, eps, c1, c2);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = refresh_bf16(N);
+    e = finish(N, nb, lr);
     if (e == hipSuccess && loss)
         e = hipMemcpyAsync(loss, N->at<float>(N->L.loss), sizeof(float), hipMemcpyDeviceToHost, N->stream);
     if (e == hipSuccess && loss) e = hipStreamSynchronize(N->stream);

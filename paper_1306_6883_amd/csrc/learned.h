@@ -33,10 +33,26 @@ inline int conv_seg(int nb, int dil) {
     while (2 * seg <= kNetG / dil && nb * kNetG / (2 * seg) >= 512) seg *= 2;
     return seg;
 }
-__global__ void k_conv32_wgrad(const __bf16 *g, const __bf16 *in, float *part, int npix, int chunk, int dil);
+template <int ALIGN>
+__global__ void k_conv32_wgrad(const __bf16 *g, const __bf16 *in, float *part, int dil, int seg);
+// Workgroups of k_conv32_wgrad (partial sums of a layer) for nb images, and the
+// most that any batch up to `batch` needs.
+inline int wgrad_blocks(int nb, int dil) { return nb * kNetG / conv_seg(nb, dil); }
+inline int wgrad_blocks_max(int batch) {
+    int most = 0;
+    for (int nb = 1; nb <= batch; ++nb)
+        for (int l = 1; l <= 4; ++l)
+            if (wgrad_blocks(nb, net_dilation(l)) > most) most = wgrad_blocks(nb, net_dilation(l));
+    return most;
+}
+constexpr int kSumGroups = 32;    // first-stage groups of the partial-sum reduction
+constexpr int kLossBlocks = 256;  // workgroups (partial sums) of k_mse
 __global__ void k_sum_partials(const float *part, int count, int len, float *out);
-__global__ void k_sum_partials_grouped(const float *part, int count, int len, int groups, float *out);
-__global__ void k_transpose_flip(const __bf16 *w, __bf16 *wt);
+__global__ void k_to_bf16(const float *a, __bf16 *w16, __bf16 *w16lo, __bf16 *wt16, int count);
+template <bool ADAM>
+__global__ void k_finish(const float *groups, float *grad, const double *lpart, int pixels, float *loss, float *w,
+                         float *m, float *v, __bf16 *w16, __bf16 *w16lo, __bf16 *wt16, float lr, float b1, float b2,
+                         float eps, float c1, float c2);
 __global__ void k_conv_in(const float *x, const float *w1, __bf16 *out, __bf16 *out_lo, int per, int dil);
 __global__ void k_conv_out(const __bf16 *in, const __bf16 *in_lo, const float *w6, float *y);
 __global__ void k_conv_out_bwd(const float *dy, const float *w6, __bf16 *g, int per, int dil);
@@ -51,10 +67,6 @@ template <bool LAST>
 __global__ void k_wgrad_small(const __bf16 *act, const __bf16 *act_lo, const float *vec, float *part, int chunk,
                               int dil);
 __global__ void k_mse(const float *y, const float *t, float *dy, double *part, int count);
-__global__ void k_loss_finish(const double *part, int blocks, int count, float *loss);
-__global__ void k_adam(float *w, const float *g, float *m, float *v, __bf16 *w16, int count, float lr, float b1,
-                       float b2, float eps, float c1, float c2);
-__global__ void k_to_bf16(const float *a, __bf16 *b, __bf16 *lo, int count);
 __global__ void k_encode(const double *f, long pitch, int n, const double *sumsq, float *out);
 constexpr int kRelaxThreads = 1024;
 __global__ void k_coarse_relax(const float *y, const float *x, const double *sumsq, int nfine, double length,

@@ -256,116 +256,222 @@ template __global__ void k_conv32<false>(const __bf16 *, const __bf16 *, const _
 
 // Weight gradient of a 32 -> 32 layer:
 //   dw[co][tap][ci] = sum_{b, y, x} g[b][y][x][co] * in[b][y + dy][x + dx][ci]
-// K runs over pixels, which are the strided dimension of the pixel-major
-// layout, so each operand tile (16 pixels x 32 channels, 1 KB) is loaded with
-// one 16-byte load per lane (pixel l / 4, channels 8 (l % 4) ..), stored
-// transposed in the wave's own LDS slot ([channel][pixel]) and read back as one
-// 16-byte LDS load per lane (channel l % 32, pixels 8 (l / 32) ..).  Runs of 16
-// pixels start at multiples of 16, so a run lies in one row; shifted runs wrap
-// pixel by pixel.  Three wavefronts share a chunk of `chunk` pixels (a
-// multiple of 16), one per row of three taps, and write the chunk's
-// 9 x 32 x 32 partial sums; the next run's tiles load during this run's
-// products.
+// K runs over pixels, the strided dimension of the pixel-major layout, so rows
+// are transposed once as they enter LDS ([channel][pixel], pixel pairs packed
+// into words) and serve all nine taps from there: a workgroup of four
+// wavefronts walks rows `dil` apart as k_conv32 does, input rows in a ring of
+// four with 16 wrapped columns on either side (the largest dilation here),
+// gradient rows in a ring of two.  A wavefront takes 32 pixels of the row, two
+// steps of 16, against the nine taps' shifted columns: 18 MFMAs into nine
+// accumulators.  A channel's row of pixels is an odd number of 16-byte units
+// long, so an operand's 16-byte reads lie in 16 different bank groups.  The
+// four wavefronts' sums meet in LDS; per workgroup 9 x 32 x 32 partial sums.
+// (The transposition used to be redone per tap, by two-byte LDS stores.
+// Measured, 32 images: 77 -> 22 us a layer with dilation 8 or 16, 26 with 4 and
+// 30 with 2, whose shifted reads are 8 and 4 bytes wide.)
+// ALIGN: alignment of a shifted 16-byte read, min(16, 2 dil).
 namespace {
-// Order this wave's LDS writes before its later LDS reads of other lanes'
-// data (a wave's LDS operations complete in issue order; this keeps the
-// compiler from reordering them).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ __forceinline__ void store_transposed(__bf16 (*tile)[16], int px, int cg, bf16x8 v) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tile[cg + j][px] = v[j];
+constexpr int kPadX = 16;
+constexpr int kInStride = kNetG + 2 * kPadX + 8;  // 336 bytes, 21 units
+constexpr int kGStride = kNetG + 8;               // 272 bytes, 17 units
+template <int ALIGN>
+__device__ __forceinline__ bf16x8 lds8(const __bf16 *p) {
+    bf16x8 v;
+    if constexpr (ALIGN >= 16) {
+        v = *reinterpret_cast<const bf16x8 *>(p);
+    } else if constexpr (ALIGN == 8) {
+        const uint2 *q = reinterpret_cast<const uint2 *>(p);
+        const uint2 u0 = q[0], u1 = q[1];
+        v = __builtin_bit_cast(bf16x8, uint4{u0.x, u0.y, u1.x, u1.y});
+    } else {
+        const unsigned *q = reinterpret_cast<const unsigned *>(p);
+        v = __builtin_bit_cast(bf16x8, uint4{q[0], q[1], q[2], q[3]});
+    }
+    return v;
 }
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_conv32_wgrad(const __bf16 *__restrict__ g, const __bf16 *__restrict__ in,
-                                                      float *__restrict__ part, int npix, int chunk, int dil) {
-    __shared__ __attribute__((aligned(16))) __bf16 lds[4][4][kNetC][16];
-    const int lane = threadIdx.x & 63;
-    const int wl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = xcd_block() * 4 + wl;
-    const int nchunks = (npix + chunk - 1) / chunk;
-    if (wave >= 3 * nchunks) return;
-    const int ck = wave / 3, trow = wave - 3 * ck;  // pixel chunk, tap row (taps 3 trow .. 3 trow + 2)
-    __bf16(*tl)[kNetC][16] = lds[wl];              // tile 0: g, tiles 1..3: shifted inputs
-    const int r = lane & 31, hk = lane >> 5;        // operand lane roles
-    const int px = lane >> 2, cg = 8 * (lane & 3);  // loader lane roles
-    f32x16 acc[3];
+template <int ALIGN>
+__global__ __launch_bounds__(256, 2) void k_conv32_wgrad(const __bf16 *__restrict__ g, const __bf16 *__restrict__ in,
+                                                         float *__restrict__ part, int dil, int seg) {
+    constexpr int kInBytes = 4 * kNetC * kInStride * 2, kGBytes = 2 * kNetC * kGStride * 2;
+    constexpr int kRed = 3 * 16 * 64;  // floats of one wavefront's three taps
+    static_assert(4 * kRed * 4 <= kInBytes + kGBytes, "the final sums reuse the rows' space");
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kInBytes + kGBytes];
+    __bf16 *tin = reinterpret_cast<__bf16 *>(lds);                // [4][32][kInStride]
+    __bf16 *tg = reinterpret_cast<__bf16 *>(lds + kInBytes);      // [2][32][kGStride]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wib = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chain = kNetG / dil, segs = chain / seg;
+    const int blk = xcd_block();
+    int q = blk;
+    const int i0 = (q % segs) * seg;
+    q /= segs;
+    const int y0 = q % dil, b = q / dil;
+    const size_t img = (size_t)b * kNetG * kNetG * kNetC;
+    auto row_at = [&](int i) { return img + (size_t)(y0 + dil * ((i0 + i) & (chain - 1))) * kNetG * kNetC; };
+    // loader roles: pixels 2 pp, 2 pp + 1, channels c8 .. c8 + 7
+    const int pp = tid >> 2, c8 = 8 * (tid & 3);
+    bf16x8 vi[2], vg[2];
+    auto fetch = [&](const __bf16 *src, int i, bf16x8 (&v)[2]) {
+        const __bf16 *p = src + row_at(i) + (size_t)(2 * pp) * kNetC + c8;
+        v[0] = load8(p);
+        v[1] = load8(p + kNetC);
+    };
+    auto put_in = [&](int slot) {
+        unsigned *t = reinterpret_cast<unsigned *>(tin + slot * kNetC * kInStride);
 #pragma unroll
-    for (int t = 0; t < 3; ++t) acc[t] = f32x16{};
-    const int p0 = ck * chunk;
-    const int p1 = min(p0 + chunk, npix);
-    bf16x8 v[4];
-    auto load_run = [&](int p) {
-        const int bb = p / (kNetG * kNetG);
-        const int rem = p - bb * kNetG * kNetG;
-        const int y = rem / kNetG, x0 = rem % kNetG;
-        const __bf16 *img = in + (size_t)bb * kNetG * kNetG * kNetC;
-        v[0] = load8(g + (size_t)(p + px) * kNetC + cg);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int t = 3 * trow + k;
-            const int ys = wrapg(y + tap_dy(t, dil));
-            const int xs = wrapg(x0 + px + tap_dx(t, dil));
-            v[1 + k] = load8(img + ((size_t)ys * kNetG + xs) * kNetC + cg);
+        for (int k = 0; k < 8; ++k) {
+            const unsigned u = pack2(vi[0][k], vi[1][k]);
+            unsigned *r = t + (c8 + k) * (kInStride / 2) + kPadX / 2 + pp;
+            r[0] = u;
+            if (pp < kPadX / 2) r[kNetG / 2] = u;                 // columns 128 .. 143
+            if (pp >= (kNetG - kPadX) / 2) r[-(kNetG / 2)] = u;   // columns -16 .. -1
         }
     };
-    load_run(p0);
-    for (int p = p0; p < p1; p += 16) {
-        wave_lds_sync();  // the previous run's operand reads are done before the tiles are rewritten
+    auto put_g = [&](int slot) {
+        unsigned *t = reinterpret_cast<unsigned *>(tg + slot * kNetC * kGStride);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) store_transposed(tl[k], px, cg, v[k]);
-        if (p + 16 < p1) load_run(p + 16);  // next run's tiles in flight during this run's products
-        wave_lds_sync();
-        const bf16x8 av = load8(&tl[0][r][8 * hk]);  // A (32 co x 16 px)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const bf16x8 bv = load8(&tl[1 + k][r][8 * hk]);  // B (16 px x 32 ci)
-            acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[k], 0, 0, 0);
-        }
+        for (int k = 0; k < 8; ++k) t[(c8 + k) * (kGStride / 2) + pp] = pack2(vg[0][k], vg[1][k]);
+    };
+    for (int i = -1; i < 2; ++i) {
+        fetch(in, i, vi);
+        put_in(i + 1);
     }
-    float *o = part + (size_t)ck * 9 * kNetC * kNetC;
+    fetch(g, 0, vg);
+    put_g(0);
+    const int r = lane & 31, hk = lane >> 5;  // operand lane roles
+    f32x16 acc[9];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int co = 8 * (j / 4) + 4 * hk + (j % 4);
-            o[((size_t)co * 9 + 3 * trow + k) * kNetC + r] = acc[k][j];
+    for (int t = 0; t < 9; ++t) acc[t] = f32x16{};
+    __syncthreads();
+    for (int i = 0; i < seg; ++i) {
+        if (i + 1 < seg) {
+            fetch(in, i + 2, vi);
+            fetch(g, i + 1, vg);
         }
+        const __bf16 *gr = tg + ((i & 1) * kNetC + r) * kGStride + 32 * wib + 8 * hk;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bf16x8 av = lds8<16>(gr + 16 * h);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const __bf16 *ir = tin + (((i + t / 3) & 3) * kNetC + r) * kInStride + kPadX + 32 * wib + 8 * hk +
+                                   16 * h + (t % 3 - 1) * dil;
+                const bf16x8 bv = t % 3 == 1 ? lds8<16>(ir) : lds8<ALIGN>(ir);
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[t], 0, 0, 0);
+            }
+        }
+        if (i + 1 < seg) {
+            put_in((i + 3) & 3);  // the slot of walk row i - 2, last read two rows ago
+            put_g((i + 1) & 1);   // the slot of gradient row i - 1
+        }
+        __syncthreads();
+    }
+    float *red = reinterpret_cast<float *>(lds);
+    float *o = part + (size_t)blk * 9 * kNetC * kNetC;
+#pragma unroll
+    for (int t0 = 0; t0 < 9; t0 += 3) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) red[wib * kRed + (16 * t + j) * 64 + lane] = acc[t0 + t][j];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kRed / 256; ++k) {
+            const int idx = tid + 256 * k;
+            const int l = idx & 63, j = (idx >> 6) & 15, t = idx >> 10;
+            const float s = ((red[idx] + red[kRed + idx]) + red[2 * kRed + idx]) + red[3 * kRed + idx];
+            const int co = 8 * (j / 4) + 4 * (l >> 5) + (j % 4);
+            o[((size_t)co * 9 + t0 + t) * kNetC + (l & 31)] = s;
+        }
+        __syncthreads();
+    }
 }
+template __global__ void k_conv32_wgrad<4>(const __bf16 *, const __bf16 *, float *, int, int);
+template __global__ void k_conv32_wgrad<8>(const __bf16 *, const __bf16 *, float *, int, int);
+template __global__ void k_conv32_wgrad<16>(const __bf16 *, const __bf16 *, float *, int, int);
 
-// out[i] = sum over `count` partial vectors of length len, in a fixed order.
-__global__ void k_sum_partials(const float *__restrict__ part, int count, int len, float *__restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= len) return;
-    float s = 0.f;
-    for (int k = 0; k < count; ++k) s += part[(size_t)k * len + i];
-    out[i] = s;
-}
-
-// Partial sums, first stage: out[grp][i] = sum of partials k = grp, grp + groups, ...
-// (grid: x over i, y over groups); the second stage is k_sum_partials over the groups.
-__global__ void k_sum_partials_grouped(const float *__restrict__ part, int count, int len, int groups,
-                                       float *__restrict__ out) {
+// Partial sums, first stage, in a fixed order: out[grp][i] = sum of partials
+// k = grp, grp + kSumGroups, ... (grid: x over i, y over the groups, whose
+// stride in `out` is that of the whole parameter vector).
+__global__ __launch_bounds__(256) void k_sum_partials(const float *__restrict__ part, int count, int len,
+                                                      float *__restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int grp = blockIdx.y;
     if (i >= len) return;
     float s = 0.f;
-    for (int k = grp; k < count; k += groups) s += part[(size_t)k * len + i];
-    out[(size_t)grp * len + i] = s;
+#pragma unroll 8
+    for (int k = grp; k < count; k += kSumGroups) s += part[(size_t)k * len + i];
+    out[(size_t)grp * kNetParams + i] = s;
 }
 
-// wt[ci][tap][co] = w[co][8 - tap][ci]: the input gradient of a layer is the
-// same convolution with these weights applied to the output gradient.
-__global__ void k_transpose_flip(const __bf16 *__restrict__ w, __bf16 *__restrict__ wt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kNetC * 9 * kNetC) return;
-    const int ci = i / (9 * kNetC), t = (i / kNetC) % 9, co = i % kNetC;
-    wt[i] = w[((size_t)co * 9 + (8 - t)) * kNetC + ci];
+namespace {
+// Parameter i as the layers read it: a BF16 (hi, lo) pair, and for the 32 -> 32
+// layers the transposed, tap-flipped copy wt[ci][tap][co] = w[co][8 - tap][ci]
+// (the input gradient of a layer is the same convolution with those weights).
+__device__ __forceinline__ void store_weight(int i, float a, __bf16 *w16, __bf16 *w16lo, __bf16 *wt16) {
+    const __bf16 h = (__bf16)a;
+    w16[i] = h;
+    w16lo[i] = (__bf16)(a - (float)h);
+    const int q = i - kW0;
+    if (q >= 0 && q < 4 * kWmid) {
+        const int l = q / kWmid, r = q - l * kWmid;
+        const int co = r / (9 * kNetC), t = (r / kNetC) % 9, ci = r % kNetC;
+        wt16[l * kWmid + (ci * 9 + (8 - t)) * kNetC + co] = h;
+    }
 }
+}  // namespace
+
+// Parameters set from outside.
+__global__ void k_to_bf16(const float *__restrict__ a, __bf16 *__restrict__ w16, __bf16 *__restrict__ w16lo,
+                          __bf16 *__restrict__ wt16, int count) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) store_weight(i, a[i], w16, w16lo, wt16);
+}
+
+// End of a backward pass, every parameter at once: the groups' sums into the
+// gradient; the loss (workgroup 0) from k_mse's partial sums; and, ADAM, the
+// optimizer's step on the FP32 master weights with the copies the layers read.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_finish(const float *__restrict__ groups, float *__restrict__ grad,
+                                                const double *__restrict__ lpart, int pixels,
+                                                float *__restrict__ loss, float *__restrict__ w, float *__restrict__ m,
+                                                float *__restrict__ v, __bf16 *__restrict__ w16,
+                                                __bf16 *__restrict__ w16lo, __bf16 *__restrict__ wt16, float lr,
+                                                float b1, float b2, float eps, float c1, float c2) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < kNetParams) {
+        float gi = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < kSumGroups; ++k) gi += groups[(size_t)k * kNetParams + i];
+        grad[i] = gi;
+        if constexpr (ADAM) {
+            const float mi = b1 * m[i] + (1.f - b1) * gi;
+            const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+            m[i] = mi;
+            v[i] = vi;
+            const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+            w[i] = wi;
+            store_weight(i, wi, w16, w16lo, wt16);
+        }
+    }
+    if (blockIdx.x == 0) {
+        static_assert(kLossBlocks == 256, "one partial sum per thread");
+        __shared__ double red[4];
+        double s = lpart[threadIdx.x];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) *loss = (float)((((red[0] + red[1]) + red[2]) + red[3]) / pixels);
+    }
+}
+template __global__ void k_finish<false>(const float *, float *, const double *, int, float *, float *, float *,
+                                         float *, __bf16 *, __bf16 *, __bf16 *, float, float, float, float, float,
+                                         float);
+template __global__ void k_finish<true>(const float *, float *, const double *, int, float *, float *, float *, float *,
+                                        __bf16 *, __bf16 *, __bf16 *, float, float, float, float, float, float);
 
 // The 1-channel layers move 32 channels of BF16 per pixel for a few hundred
 // operations: bound by memory once their accesses are whole cache lines.  Four
@@ -586,40 +692,6 @@ __global__ __launch_bounds__(256) void k_mse(const float *__restrict__ y, const 
         __syncthreads();
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ void k_loss_finish(const double *__restrict__ part, int blocks, int count, float *__restrict__ loss) {
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < blocks; ++i) s += part[i];
-        *loss = (float)(s / count);
-    }
-}
-
-// Adam on FP32 master weights; refreshes the BF16 copy of the 32 -> 32 layers.
-__global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
-                       float *__restrict__ v, __bf16 *__restrict__ w16, int count, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    w[i] = wi;
-    w16[i] = (__bf16)wi;
-}
-
-// BF16 copy of the weights as a (hi, lo) pair: hi = bf16(a), lo = bf16(a - hi).
-__global__ void k_to_bf16(const float *__restrict__ a, __bf16 *__restrict__ b, __bf16 *__restrict__ lo, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) {
-        const __bf16 h = (__bf16)a[i];
-        b[i] = h;
-        if (lo) lo[i] = (__bf16)(a[i] - (float)h);
-    }
 }
 
 // Scale of a right-hand side: its RMS over the valid cells, sqrt(sum f^2 / n^2);
