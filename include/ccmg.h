@@ -448,7 +448,8 @@ int ccmg_plan_autotune(ccmg_plan *plan, const double *d_f, double *d_phi, ptrdif
  * the level; 1 <= wpb <= 4 (bands of 8 and 16 rows that are held in registers
  * whole run one wave per workgroup).  ty = 0 runs as ty = 8 (levels below the
  * finest with at least 64 cells per side that are not in the one-workgroup
- * tail).  kind 2 = the fused finest launch of FP64 solves, 3 = its FP32 form in
+ * tail).  The 64 x 64 level runs in one launch with the tail wherever its
+ * correction starts from zero (its shapes are then unused).  kind 2 = the fused finest launch of FP64 solves, 3 = its FP32 form in
  * mixed-precision steps (level 0 only, ty even and >= 8).  Levels below the finest that are not
  * in the tail, run as a visit (CCMG_OPT_VISIT): kind 4 = the restricting
  * launch without the stored iterate (as kind 0), kind 5 = the visit launch

@@ -573,55 +573,29 @@ __device__ __forceinline__ T exact_bottom(const double *__restrict__ ainv, T f, 
 }
 
 template <typename T>
-__device__ void tail_body(const CoarseArgs<T> &a) {
+__device__ __forceinline__ TailSides<T> tail_sides(const int *bc) {
     const int lane = threadIdx.x & 63;
     TailSides<T> sd;
-    sd.px = a.bc[CCMG_XLO] == CCMG_BC_PERIODIC;
-    sd.py = a.bc[CCMG_YLO] == CCMG_BC_PERIODIC;
-    sd.sxl = a.bc[CCMG_XLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
-    sd.sxh = a.bc[CCMG_XHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
-    sd.syl = a.bc[CCMG_YLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
-    sd.syh = a.bc[CCMG_YHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.px = bc[CCMG_XLO] == CCMG_BC_PERIODIC;
+    sd.py = bc[CCMG_YLO] == CCMG_BC_PERIODIC;
+    sd.sxl = bc[CCMG_XLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.sxh = bc[CCMG_XHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.syl = bc[CCMG_YLO] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
+    sd.syh = bc[CCMG_YHI] == CCMG_BC_DIRICHLET ? T(-1) : T(1);
     sd.I = lane & 15;
     sd.g = lane >> 4;
     sd.odd = lane & 1;
     sd.up = ((lane + 16) & 63) * 4;
     sd.dn = ((lane + 48) & 63) * 4;
+    return sd;
+}
+
+// One V-cycle of the 32 x 32 level held in P5, F5 (by one wavefront).
+template <typename T>
+__device__ __forceinline__ void tail_core(const CoarseArgs<T> &a, const TailSides<T> &sd, T (&P5)[2][8], T (&F5)[2][8]) {
     auto consts = [&](int l) {
         return OpConst<T>{T(a.cc[l]), T(a.invd[l]), T(a.alpha), T(a.beta), T(a.ih2[l])};
     };
-    // 32 x 32: every load before the skip flag is looked at
-    T P5[2][8], F5[2][8];
-    const int stop = a.skip ? *a.skip : 0;
-    const double shift64 = (a.load_phi && a.phi_shift) ? *a.phi_shift : 0.0;
-    {
-        const T *f = a.f + (long)(8 * sd.g + 1) * a.pf + 1 + 2 * sd.I;
-        const T *p = a.phi_in + (long)(8 * sd.g + 1) * a.pin + 1 + 2 * sd.I;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            F5[0][r] = f[(long)r * a.pf];
-            F5[1][r] = f[(long)r * a.pf + 1];
-        }
-        if (a.load_phi) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                P5[0][r] = p[(long)r * a.pin];
-                P5[1][r] = p[(long)r * a.pin + 1];
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) P5[0][r] = P5[1][r] = T(0);
-        }
-    }
-    if (stop) return;
-    const T shift = T(shift64);
-    if (a.load_phi) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            P5[0][r] -= shift;
-            P5[1][r] -= shift;
-        }
-    }
     if (a.sub_top_mean) {
         double t = 0.0;
 #pragma unroll
@@ -787,6 +761,44 @@ __device__ void tail_body(const CoarseArgs<T> &a) {
         }
     }
     relax32(P5, F5, sd, k5, a.nu2);
+}
+
+template <typename T>
+__device__ void tail_body(const CoarseArgs<T> &a) {
+    const TailSides<T> sd = tail_sides<T>(a.bc);
+    // every load before the skip flag is looked at
+    T P5[2][8], F5[2][8];
+    const int stop = a.skip ? *a.skip : 0;
+    const double shift64 = (a.load_phi && a.phi_shift) ? *a.phi_shift : 0.0;
+    {
+        const T *f = a.f + (long)(8 * sd.g + 1) * a.pf + 1 + 2 * sd.I;
+        const T *p = a.phi_in + (long)(8 * sd.g + 1) * a.pin + 1 + 2 * sd.I;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            F5[0][r] = f[(long)r * a.pf];
+            F5[1][r] = f[(long)r * a.pf + 1];
+        }
+        if (a.load_phi) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                P5[0][r] = p[(long)r * a.pin];
+                P5[1][r] = p[(long)r * a.pin + 1];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) P5[0][r] = P5[1][r] = T(0);
+        }
+    }
+    if (stop) return;
+    const T shift = T(shift64);
+    if (a.load_phi) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            P5[0][r] -= shift;
+            P5[1][r] -= shift;
+        }
+    }
+    tail_core(a, sd, P5, F5);
     T *o = a.phi_out + (long)(8 * sd.g + 1) * a.pout + 1 + 2 * sd.I;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -795,11 +807,247 @@ __device__ void tail_body(const CoarseArgs<T> &a) {
     }
 }
 
+// Total of `count` partial sums in the row march's order (every 64th value per
+// lane, loaded 16 at a time, then a butterfly).
+__device__ __forceinline__ double tail_sum_partials(const double *p, int count) {
+    const int lane = threadIdx.x & 63;
+    double s = 0.0;
+    for (int i = lane; i < count; i += 16 * 64) {
+        double v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = i + 64 * k < count ? p[i + 64 * k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (i + 64 * k < count) s += v[k];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    return s;
+}
+
+// ---- a 64 x 64 level on four wavefronts, around the tail -----------------------
+// The level above the tail has 4096 cells: as launches of its own (two per
+// cycle, 4.5 - 5.5 us each, half of it the launch) it cost as much as the
+// tail.  Four wavefronts hold it in registers -- lane (I, G), G = 4 wave + g:
+// columns 4I .. 4I + 3 of rows 4G .. 4G + 3 -- with x neighbours by DPP
+// rotations as in the tail; a row group's first and last rows go through LDS
+// (by colour, so one barrier per sweep), and the coarse right-hand side and
+// correction too, for the first wavefront's tail.  The arithmetic of a cell is
+// the row march's (products fused into sums within an expression only).
+// FP64 Helmholtz: 11.2 us for 4.6 + 7.3 + 4.6 as three launches; periodic, with
+// means, 13.8 for 5.5 + 8.9 + 5.5.
+template <typename T>
+struct L64 {
+    static constexpr int CS = 34;                 // row stride of the coarse field in LDS
+    T P[4][4], F[4][4];                           // [column][row]
+    T (*E)[2][16][32];                            // [colour][first / last row][G][cells of the colour]
+    T *C;                                         // [32][CS]
+    int G;
+
+    __device__ __forceinline__ void publish(int q) {  // the edge rows' cells of colour q
+        const int k = 2 * (threadIdx.x & 15);
+        E[q][0][G][k] = q ? P[1][0] : P[0][0];
+        E[q][0][G][k + 1] = q ? P[3][0] : P[2][0];
+        E[q][1][G][k] = q ? P[0][3] : P[1][3];
+        E[q][1][G][k + 1] = q ? P[2][3] : P[3][3];
+    }
+    // neighbours of cell (c, r); s[], n[]: the rows below row 0 and above row 3
+    __device__ __forceinline__ Nb<T> around(int c, int r, const T (&s)[4], const T (&n)[4], const TailSides<T> &sd) const {
+        const T self = P[c][r];
+        Nb<T> v;
+        v.e = c < 3 ? P[c < 3 ? c + 1 : 3][r] : sd.east(sd.I == 15, self, from_right16<1>(P[0][r]));
+        v.w = c > 0 ? P[c > 0 ? c - 1 : 0][r] : sd.west(sd.I == 0, self, from_left16<1>(P[3][r]));
+        v.n = r < 3 ? P[c][r < 3 ? r + 1 : 3] : sd.north(G == 15, self, n[c]);
+        v.s = r > 0 ? P[c][r > 0 ? r - 1 : 0] : sd.south(G == 0, self, s[c]);
+        return v;
+    }
+    // one colour sweep; the other colour's edges are published
+    template <int Q>
+    __device__ __forceinline__ void sweep(const TailSides<T> &sd, const OpConst<T> &k) {
+#pragma clang fp contract(on)
+        const int at = 2 * sd.I;
+        T s[4], n[4];
+        s[Q] = E[1 - Q][1][(G + 15) & 15][at];
+        s[Q + 2] = E[1 - Q][1][(G + 15) & 15][at + 1];
+        n[1 - Q] = E[1 - Q][0][(G + 1) & 15][at];
+        n[3 - Q] = E[1 - Q][0][(G + 1) & 15][at + 1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = (r + Q) & 1; c < 4; c += 2) {
+                const Nb<T> v = around(c, r, s, n, sd);
+                P[c][r] = (F[c][r] + k.cc * (((v.e + v.w) + v.n) + v.s)) * k.invd;
+            }
+        publish(Q);
+        __syncthreads();
+    }
+    // relaxations; zero: from a zero iterate, whose first red sweep reads no neighbour
+    __device__ __forceinline__ void relax(const TailSides<T> &sd, const OpConst<T> &k, int iters, bool zero) {
+        for (int it = 0; it < iters; ++it) {
+            if (it == 0 && zero) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = r & 1; c < 4; c += 2) P[c][r] = F[c][r] * k.invd;
+                publish(0);
+                __syncthreads();
+            } else {
+                sweep<0>(sd, k);
+            }
+            sweep<1>(sd, k);
+        }
+    }
+    // both colours' edges around the lane's cells
+    __device__ __forceinline__ void edges(T (&s)[4], T (&n)[4], const TailSides<T> &sd) const {
+        const int at = 2 * sd.I;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            s[c] = E[1 - (c & 1)][1][(G + 15) & 15][at + (c >> 1)];
+            n[c] = E[c & 1][0][(G + 1) & 15][at + (c >> 1)];
+        }
+    }
+    __device__ __forceinline__ T resid(int c, int r, const T (&s)[4], const T (&n)[4], const TailSides<T> &sd,
+                                       const OpConst<T> &k) const {
+#pragma clang fp contract(on)
+        const Nb<T> v = around(c, r, s, n, sd);
+        const T p = P[c][r];
+        const T lap = ((((v.e - p) + (v.w - p)) + (v.n - p)) + (v.s - p)) * k.ih2;
+        return F[c][r] - (k.alpha * p - k.beta * lap);
+    }
+    // the residual's four-cell averages into C
+    __device__ __forceinline__ void restrict_to(const TailSides<T> &sd, const OpConst<T> &k) {
+        T s[4], n[4];
+        edges(s, n, sd);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const T r00 = resid(2 * a, 2 * b, s, n, sd, k), r01 = resid(2 * a + 1, 2 * b, s, n, sd, k);
+                const T r10 = resid(2 * a, 2 * b + 1, s, n, sd, k), r11 = resid(2 * a + 1, 2 * b + 1, s, n, sd, k);
+                C[(2 * G + b) * CS + 2 * sd.I + a] = T(0.25) * (((r00 + r01) + r10) + r11);
+            }
+    }
+    // sums of r^2 and phi over the lane's cells
+    __device__ __forceinline__ void norm(const TailSides<T> &sd, const OpConst<T> &k, double &r2, double &ph) const {
+        T s[4], n[4];
+        edges(s, n, sd);
+        r2 = ph = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double q = (double)resid(c, r, s, n, sd, k);
+                r2 += q * q;
+                ph += (double)P[c][r];
+            }
+    }
+    // P += prolongation of the coarse correction in C
+    __device__ __forceinline__ void prolong(const TailSides<T> &sd) {
+        T m[4][2], wv[2], ev[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T *row = C + ((2 * G + q + 31) & 31) * CS + 2 * sd.I;
+            m[q][0] = row[0];
+            m[q][1] = row[1];
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            wv[b] = sd.west(sd.I == 0, m[1 + b][0], from_left16<1>(m[1 + b][1]));
+            ev[b] = sd.east(sd.I == 15, m[1 + b][1], from_right16<1>(m[1 + b][0]));
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const T e = m[1 + b][a];
+                const T ee = a ? ev[b] : m[1 + b][1], ew = a ? m[1 + b][0] : wv[b];
+                const T en = b ? sd.north(G == 15, e, m[3][a]) : m[2][a];
+                const T es = b ? m[1][a] : sd.south(G == 0, e, m[0][a]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        P[2 * a + x][2 * b + h] = P[2 * a + x][2 * b + h] +
+                                                  slopes(e, ee, ew, en, es, x ? T(0.25) : T(-0.25),
+                                                         h ? T(0.25) : T(-0.25));
+            }
+    }
+    // one V-cycle (whole workgroup); the tail runs on the first wavefront
+    __device__ __forceinline__ void cycle(const CoarseArgs<T> &a, const TailSides<T> &sd, const OpConst<T> &k, bool zero) {
+        relax(sd, k, a.nu1, zero);
+        restrict_to(sd, k);
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            T P5[2][8], F5[2][8];
+            T *c = C + 8 * sd.g * CS + 2 * sd.I;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    F5[x][r] = c[r * CS + x];
+                    P5[x][r] = T(0);
+                }
+            tail_core(a, sd, P5, F5);
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) c[r * CS + x] = P5[x][r];
+        }
+        __syncthreads();
+        prolong(sd);
+        publish(1);  // the red sweep reads the black edges
+        publish(0);
+        __syncthreads();
+        relax(sd, k, a.nu2, false);
+    }
+};
+
 }  // namespace
 
 template <typename T>
 __global__ __launch_bounds__(64) void k_tail(const CoarseArgs<T> a) {
     tail_body<T>(a);
+}
+
+// A 64 x 64 level below the finest and its tail, from a zero iterate.
+template <typename T>
+__global__ __launch_bounds__(256) void k_tail64(const Tail64Args<T> a) {
+    __shared__ T edge[2][2][16][32];
+    __shared__ T coarse[32 * L64<T>::CS];
+    const TailSides<T> sd = tail_sides<T>(a.c.bc);
+    const OpConst<T> k{T(a.cc), T(a.invd), T(a.c.alpha), T(a.c.beta), T(a.ih2)};
+    L64<T> lv;
+    lv.E = edge;
+    lv.C = coarse;
+    lv.G = 4 * (threadIdx.x >> 6) + sd.g;
+    const int stop = a.c.skip ? *a.c.skip : 0;
+    const T *f = a.c.f + (long)(4 * lv.G + 1) * a.c.pf + 1 + 4 * sd.I;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            lv.F[c][r] = f[(long)r * a.c.pf + c];
+            lv.P[c][r] = T(0);
+        }
+    if (a.fmean_part) {
+        const T m = T(tail_sum_partials(a.fmean_part, a.fmean_count) / 4096.0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) lv.F[c][r] -= m;
+    }
+    if (stop) return;  // uniform
+    if (a.c.nu1 == 0) {  // no sweep publishes the (zero) edges
+        lv.publish(0);
+        lv.publish(1);
+        __syncthreads();
+    }
+    lv.cycle(a.c, sd, k, true);
+    T *o = a.c.phi_out + (long)(4 * lv.G + 1) * a.c.pout + 1 + 4 * sd.I;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[(long)r * a.c.pout + c] = lv.P[c][r];
 }
 
 template <int NT, typename T, bool DIRECT>
@@ -900,6 +1148,21 @@ hipError_t launch_coarse(const CoarseArgs<T> &a0, hipStream_t s) {
     else hipLaunchKernelGGL((k_coarse<NT, T, false>), dim3(1), dim3(NT), 0, s, a);
     return hipGetLastError();
 }
+
+template <typename T>
+hipError_t launch_tail64(const Tail64Args<T> &a0, hipStream_t s) {
+    Tail64Args<T> a = a0;
+    if (a.c.n_top != kCoarseMax || a.c.load_phi) return hipErrorInvalidValue;
+    coarse_fill_consts(a.c);
+    const bool direct = a.c.n_bottom >= 4;
+    if (direct && (a.c.n_bottom > kDirectMax || (a.c.n_bottom & (a.c.n_bottom - 1)) || !a.c.ainv))
+        return hipErrorInvalidValue;
+    if (!direct) a.c.n_bottom = 0;
+    hipLaunchKernelGGL(k_tail64<T>, dim3(1), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+template hipError_t launch_tail64<double>(const Tail64Args<double> &, hipStream_t);
+template hipError_t launch_tail64<float>(const Tail64Args<float> &, hipStream_t);
 
 template <typename T>
 hipError_t launch_coarse_list(const CoarseArgs<T> *list, int count, hipStream_t s) {

@@ -179,6 +179,18 @@ struct CoarseArgs {
     int n_bottom;
     const double *ainv;
 };
+// A 64 x 64 level below the finest and the tail under it, one workgroup, from a
+// zero iterate: c describes the tail (n_top = 32, h_top of the 32 x 32 level)
+// but for f and phi_out, which are the 64 x 64 level's.
+template <typename T>
+struct Tail64Args {
+    CoarseArgs<T> c;
+    double cc, invd, ih2;      // the 64 x 64 level's operator
+    const double *fmean_part;  // partial sums whose total / 64^2 is subtracted from f (or null)
+    int fmean_count;
+};
+template <typename T>
+hipError_t launch_tail64(const Tail64Args<T> &a, hipStream_t s);
 // Largest exact-bottom level (cells per side): its inverse is held in LDS.
 constexpr int kDirectMax = 8;
 // Inverse of (alpha - beta Lap_h) on an nb x nb level with the side rules bc

@@ -487,9 +487,15 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
         a.ih2_64 = 1.0 / (h * h);
     };
 
+    // the level above the tail (64 x 64), where its correction starts from
+    // zero, runs in one launch with it
+    const int l64 = lay.lt - 1;
+    const bool with64 = lay.lt >= 2 && lay.lev[lay.lt].n == kCoarseMax && l64 >= 1 &&
+                        (io.coarse_only || l64 > top) && !(visits_ok && P->opt_visit == 2);
+    const int ltail = with64 ? l64 : lay.lt;
     // down
     if (io.coarse_only) fpart_count[1] = io.f1_count;
-    for (int l = top; l < lay.lt; ++l) {
+    for (int l = top; l < ltail; ++l) {
         setup_bufs(l);
         const NuChain chain = split_nu(P->p.nu1);
         bool zero = io.coarse_only || l > top || io.zero;
@@ -530,7 +536,28 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
         }
     }
     // bottom part in one workgroup
-    {
+    if (with64) {
+        setup_bufs(l64);
+        Tail64Args<T> t{};
+        coarse_consts(P, lay.lt, t.c);
+        MarchArgs<T> m{};
+        fmean(l64, m);
+        t.fmean_part = m.fmean_part;
+        t.fmean_count = m.fmean_count;
+        const Buf<T> fb = fptr(l64);
+        t.c.f = fb.p;
+        t.c.pf = fb.pitch;
+        t.c.phi_out = cur[l64].p;
+        t.c.pout = cur[l64].pitch;
+        t.c.skip = io.skip;
+        t.c.sub_top_mean = t.c.singular = P->singular ? 1 : 0;
+        const double h = lay.lev[l64].h, c = P->p.beta / (h * h);
+        t.cc = c;
+        t.invd = 1.0 / (P->p.alpha + 4.0 * c);
+        t.ih2 = 1.0 / (h * h);
+        e = launch_tail64<T>(t, s);
+        if (e != hipSuccess) return e;
+    } else {
         const int l = lay.lt;
         setup_bufs(l);
         CoarseArgs<T> c{};
@@ -552,7 +579,7 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
         if (e != hipSuccess) return e;
     }
     // up
-    for (int l = lay.lt - 1; l >= top; --l) {
+    for (int l = ltail - 1; l >= top; --l) {
         if (visited[l]) {
             MarchArgs<T> a{};
             level_consts(P, l, a);
