@@ -132,7 +132,10 @@ int ccmg_plan_destroy(ccmg_plan *plan);
  * pre-smoothing of the next in one launch (the same iterates; see
  * CCMG_OPT_FUSED); from a zero start they also take f's statistics (for the
  * checks above and ||f||) in the first cycle's first launch and check them
- * after that cycle.  On an error status (CCMG_EINCOMPAT, CCMG_ENONFINITE,
+ * after that cycle.  FP64 plans of 64 and 32 cells per side run the whole solve
+ * in one launch (the same iterates; not from a full multigrid start, while
+ * launches are timed, or, at 64, with CCMG_OPT_FUSED or CCMG_OPT_FUSED_KEEP
+ * below their defaults).  On an error status (CCMG_EINCOMPAT, CCMG_ENONFINITE,
  * ...) d_phi's contents are unspecified. */
 int ccmg_solve(ccmg_plan *plan, const double *d_f, double *d_phi, ptrdiff_t pitch, int use_guess,
                ccmg_result *out);

@@ -1050,6 +1050,204 @@ __global__ __launch_bounds__(256) void k_tail64(const Tail64Args<T> a) {
         for (int c = 0; c < 4; ++c) o[(long)r * a.c.pout + c] = lv.P[c][r];
 }
 
+// ---- whole solves of 64 x 64 and 32 x 32 grids ---------------------------------
+// A cycle of such a grid is a few microseconds of work behind three launches,
+// an event and the host's stop test.  The levels already live in one
+// workgroup's registers, so the whole solve does: V-cycles until the residual
+// is within the tolerance (or not finite, or max_cycles have run), in one
+// launch.  f's statistics come from its loads; a right-hand side that ends the
+// solve (zero, not finite, or of nonzero mean on a singular problem) does so
+// before the first cycle.  The arithmetic of a cell is the separate launches'.
+// (64 x 64 Dirichlet, 12 cycles: 345 us in 38 launches, 173 in two, of which 155
+// are this one.)
+namespace {
+// sum over the workgroup (fixed order), in every thread
+template <int NT>
+__device__ __forceinline__ double solo_sum(double v, double *red) {
+    if constexpr (NT == 64) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+        return v;
+    } else {
+        return block_sum<NT>(v, red);
+    }
+}
+struct FStats {
+    double s = 0.0, a = 0.0, q = 0.0, bad = 0.0;
+    __device__ __forceinline__ void add(double v) {
+        if (!isfinite(v)) {
+            bad += 1.0;
+        } else {
+            s += v;
+            a += fabs(v);
+            q += v * v;
+        }
+    }
+};
+// The solve around a level held in registers.  start() readies a loaded guess
+// for norm(); norm(r2, phi) gives this lane's sums, shift(m) subtracts m from
+// the iterate, cycle(zero) runs a V-cycle.  Returns false when the iterate is
+// not to be stored.
+template <int NT, typename Start, typename Norm, typename Shift, typename Cycle>
+__device__ bool solo_solve(const SoloArgs &a, double cells, FStats fs, double *red, Start &&start, Norm &&norm,
+                           Shift &&shift, Cycle &&cycle) {
+    double *info = a.out + CCMG_HISTORY;  // cycles, then f's statistics
+    fs.s = solo_sum<NT>(fs.s, red);
+    fs.a = solo_sum<NT>(fs.a, red);
+    fs.q = solo_sum<NT>(fs.q, red);
+    fs.bad = solo_sum<NT>(fs.bad, red);
+    const bool first = threadIdx.x == 0;
+    if (first) {
+        info[0] = 0.0;
+        info[1] = fs.s;
+        info[2] = fs.a;
+        info[3] = fs.q;
+        info[4] = fs.bad;
+    }
+    if (fs.bad > 0.0 || !isfinite(fs.q) || fs.q == 0.0 || (a.singular && fabs(fs.s) > 1e-12 * fs.a)) return false;
+    const double fnorm = sqrt(fs.q);
+    auto residual = [&]() -> double {
+        double r2, ph;
+        norm(r2, ph);
+        r2 = solo_sum<NT>(r2, red);
+        ph = solo_sum<NT>(ph, red);
+        if (a.singular) shift(ph / cells);
+        return sqrt(r2) / fnorm;
+    };
+    double rho = 1.0;
+    start();
+    if (a.use_guess) rho = residual();
+    if (first) a.out[0] = rho;
+    if (!isfinite(rho)) return false;
+    int k = 0;
+    while (rho > a.rtol && k < a.max_cycles) {
+        cycle(k == 0 && !a.use_guess);
+        ++k;
+        rho = residual();
+        if (first) a.out[k] = rho;
+        if (!isfinite(rho)) break;
+    }
+    if (first) info[0] = (double)k;
+    return true;
+}
+}  // namespace
+
+__global__ __launch_bounds__(256) void k_solve64(const SoloArgs a) {
+    __shared__ double edge[2][2][16][32];
+    __shared__ double coarse[32 * L64<double>::CS];
+    __shared__ double red[4];
+    const TailSides<double> sd = tail_sides<double>(a.c.bc);
+    const OpConst<double> k{a.cc, a.invd, a.c.alpha, a.c.beta, a.ih2};
+    L64<double> lv;
+    lv.E = edge;
+    lv.C = coarse;
+    lv.G = 4 * (threadIdx.x >> 6) + sd.g;
+    const double *f = a.f + (long)(4 * lv.G + 1) * a.pitch + 1 + 4 * sd.I;
+    double *p = a.phi + (long)(4 * lv.G + 1) * a.pitch + 1 + 4 * sd.I;
+    FStats fs;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            lv.F[c][r] = f[(long)r * a.pitch + c];
+            lv.P[c][r] = a.use_guess ? p[(long)r * a.pitch + c] : 0.0;
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fs.add(lv.F[c][r]);
+    auto publish = [&]() {
+        lv.publish(0);
+        lv.publish(1);
+        __syncthreads();
+    };
+    const bool store = solo_solve<256>(
+        a, 4096.0, fs, red, publish, [&](double &r2, double &ph) { lv.norm(sd, k, r2, ph); },
+        [&](double m) {  // (block sums have passed a barrier since the edges were read)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) lv.P[c][r] -= m;
+            publish();
+        },
+        [&](bool zero) { lv.cycle(a.c, sd, k, zero); });
+    if (!store) return;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p[(long)r * a.pitch + c] = lv.P[c][r];
+}
+
+__global__ __launch_bounds__(64) void k_solve32(const SoloArgs a) {
+    const TailSides<double> sd = tail_sides<double>(a.c.bc);
+    const OpConst<double> k{a.cc, a.invd, a.c.alpha, a.c.beta, a.ih2};
+    double P5[2][8], F5[2][8];
+    const double *f = a.f + (long)(8 * sd.g + 1) * a.pitch + 1 + 2 * sd.I;
+    double *p = a.phi + (long)(8 * sd.g + 1) * a.pitch + 1 + 2 * sd.I;
+    FStats fs;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            F5[c][r] = f[(long)r * a.pitch + c];
+            P5[c][r] = a.use_guess ? p[(long)r * a.pitch + c] : 0.0;
+        }
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) fs.add(F5[c][r]);
+    const bool store = solo_solve<64>(
+        a, 1024.0, fs, nullptr, [] {},
+        [&](double &r2, double &ph) {
+            double below[2], above[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                below[c] = lane_at(sd.dn, P5[c][7]);
+                above[c] = lane_at(sd.up, P5[c][0]);
+            }
+            r2 = ph = 0.0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const double self = P5[c][r];
+                    const double e = c ? sd.east(sd.I == 15, self, from_right16<1>(P5[0][r])) : P5[1][r];
+                    const double w = c ? P5[0][r] : sd.west(sd.I == 0, self, from_left16<1>(P5[1][r]));
+                    const double nn = r < 7 ? P5[c][r < 7 ? r + 1 : 7] : sd.north(sd.g == 3, self, above[c]);
+                    const double s = r > 0 ? P5[c][r > 0 ? r - 1 : 0] : sd.south(sd.g == 0, self, below[c]);
+                    const double q = k.resid(F5[c][r], self, e, w, nn, s);
+                    r2 += q * q;
+                    ph += self;
+                }
+        },
+        [&](double m) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                P5[0][r] -= m;
+                P5[1][r] -= m;
+            }
+        },
+        [&](bool) { tail_core(a.c, sd, P5, F5); });
+    if (!store) return;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) p[(long)r * a.pitch + c] = P5[c][r];
+}
+
+hipError_t launch_solo(const SoloArgs &a0, int n, hipStream_t s) {
+    SoloArgs a = a0;
+    if ((n != 32 && n != 64) || a.c.n_top != kCoarseMax || a.max_cycles >= CCMG_HISTORY) return hipErrorInvalidValue;
+    coarse_fill_consts(a.c);
+    const bool direct = a.c.n_bottom >= 4;
+    if (direct && (a.c.n_bottom > kDirectMax || (a.c.n_bottom & (a.c.n_bottom - 1)) || !a.c.ainv))
+        return hipErrorInvalidValue;
+    if (!direct) a.c.n_bottom = 0;
+    if (n == 64) hipLaunchKernelGGL(k_solve64, dim3(1), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_solve32, dim3(1), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int NT, typename T, bool DIRECT>
 __global__ __launch_bounds__(NT) void k_coarse(const CoarseArgs<T> a) {
     coarse_body<NT, T, DIRECT>(a);

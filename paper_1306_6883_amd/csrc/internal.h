@@ -191,6 +191,23 @@ struct Tail64Args {
 };
 template <typename T>
 hipError_t launch_tail64(const Tail64Args<T> &a, hipStream_t s);
+// A whole FP64 solve of a 64 x 64 or 32 x 32 grid in one launch: c describes
+// the tail's levels (32 x 32 down; sub_top_mean and singular: on the levels
+// below the finest); cc, invd, ih2 the finest level's operator.  out
+// (host-mapped): the relative residual at the start and after each cycle, then
+// from CCMG_HISTORY on the number of cycles and f's four statistics.
+struct SoloArgs {
+    CoarseArgs<double> c;
+    double cc, invd, ih2;
+    const double *f;
+    double *phi;
+    long pitch;
+    int use_guess, singular, max_cycles;
+    double rtol;
+    double *out;
+};
+constexpr int kSoloInfo = 8;
+hipError_t launch_solo(const SoloArgs &a, int n, hipStream_t s);
 // Largest exact-bottom level (cells per side): its inverse is held in LDS.
 constexpr int kDirectMax = 8;
 // Inverse of (alpha - beta Lap_h) on an nb x nb level with the side rules bc

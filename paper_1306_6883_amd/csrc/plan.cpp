@@ -1126,7 +1126,7 @@ int ccmg_plan_create(const ccmg_problem *p, void *d_ws, size_t ws_bytes, void *s
     hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&P->hpin), sizeof(double) * (CCMG_HISTORY + kScal),
                                  hipHostMallocDefault);
     if (e == hipSuccess)
-        e = hipHostMalloc(reinterpret_cast<void **>(&P->hrho), sizeof(double) * CCMG_HISTORY,
+        e = hipHostMalloc(reinterpret_cast<void **>(&P->hrho), sizeof(double) * (CCMG_HISTORY + kSoloInfo),
                           hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&P->drho), P->hrho, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&P->ev_sync[0], hipEventDisableTiming);
@@ -2120,6 +2120,69 @@ size_t ccmg_noalloc_scratch_bytes(void) { return kStaticScratchBytes; }
 
 }  // extern "C"
 
+namespace {
+// FP64 solves of 64 x 64 and 32 x 32 grids run in one launch.  Not while
+// launches are timed, from a full multigrid start, or (64 x 64) with the fused
+// finest launch switched off or its keep factor below the default: those name
+// the separate launches and what they leave behind.
+bool solo_ok(const ccmg_plan *P, int use_guess, double guess_reject) {
+    const int n = P->lay.lev[0].n;
+    if ((n != 32 && n != 64) || P->p.prec != CCMG_FP64 || P->p.max_cycles < 1 || P->timer.on) return false;
+    if ((P->opt_fmg > 0 && !use_guess) || (use_guess && std::isfinite(guess_reject))) return false;
+    return n == 32 || (P->opt_fused && P->opt_fused_keep >= 1.0);
+}
+
+int solve_solo(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t pitch, int use_guess, ccmg_result *R,
+               double *cn_f) {
+    hipStream_t s = P->stream;
+    const int n = P->lay.lev[0].n;
+    hipError_t e = hipEventRecord(P->ev_t0, s);
+    if (e == hipSuccess && cn_f)
+        e = launch_cn_rhs(d_phi, pitch, cn_f, pitch, n, P->p.bc, P->p.beta, P->lay.lev[0].h, s);
+    SoloArgs a{};
+    coarse_consts(P, P->lay.lt, a.c);
+    a.c.sub_top_mean = (P->singular && n == 64) ? 1 : 0;
+    a.c.singular = P->singular ? 1 : 0;
+    const double h = P->lay.lev[0].h, c = P->p.beta / (h * h);
+    a.cc = c;
+    a.invd = 1.0 / (P->p.alpha + 4.0 * c);
+    a.ih2 = 1.0 / (h * h);
+    a.f = d_f;
+    a.phi = d_phi;
+    a.pitch = pitch;
+    a.use_guess = use_guess ? 1 : 0;
+    a.singular = P->singular ? 1 : 0;
+    a.max_cycles = P->p.max_cycles;
+    a.rtol = P->p.rtol;
+    a.out = P->drho;
+    if (e == hipSuccess) e = launch_solo(a, n, s);
+    if (e == hipSuccess) e = launch_fill_ghosts_f64(d_phi, pitch, n, P->p.bc, nullptr, s);
+    if (e == hipSuccess) e = hipEventRecord(P->ev_t1, s);
+    if (e == hipSuccess) e = hipEventSynchronize(P->ev_t1);
+    if (e != hipSuccess) return R->status = CCMG_EHIP;
+    const double *info = P->hrho + CCMG_HISTORY;
+    const double fsum = info[1], fabs1 = info[2], f2 = info[3], fbad = info[4];
+    if (fbad > 0 || !std::isfinite(f2)) return R->status = CCMG_ENONFINITE;
+    if (f2 == 0.0) {  // phi = 0 exactly (valid and ghost cells)
+        e = hipMemset2DAsync(d_phi, sizeof(double) * pitch, 0, sizeof(double) * (n + 2), n + 2, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        return R->status = e == hipSuccess ? CCMG_OK : CCMG_EHIP;
+    }
+    if (P->singular && std::fabs(fsum) > 1e-12 * fabs1) return R->status = CCMG_EINCOMPAT;
+    const int cycles = (int)info[0];
+    for (int k = 0; k <= cycles; ++k) R->history[k] = P->hrho[k];
+    R->rel_resid0 = P->hrho[0];
+    const double rho = P->hrho[cycles];
+    if (!std::isfinite(P->hrho[0])) return R->status = CCMG_ENONFINITE;
+    float ms = 0.f;
+    hipEventElapsedTime(&ms, P->ev_t0, P->ev_t1);
+    R->ms = ms;
+    R->cycles = cycles;
+    R->rel_resid = rho;
+    return R->status = !std::isfinite(rho) ? CCMG_ENONFINITE : rho <= P->p.rtol ? CCMG_OK : CCMG_NOT_CONVERGED;
+}
+}  // namespace
+
 // ccmg_solve, and the learned solve's first attempt: with use_guess and a
 // finite guess_reject, a guess whose relative residual is not finite or above
 // guess_reject returns kGuessRejected before any cycle runs.
@@ -2130,6 +2193,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
     std::memset(R, 0, sizeof(*R));
     if (!P || !d_f || !d_phi) return R->status = CCMG_EINVAL;
     if (check_pitch(P, 0, pitch) != CCMG_OK) return R->status = CCMG_EINVAL;
+    if (solo_ok(P, use_guess, guess_reject)) return solve_solo(P, d_f, d_phi, pitch, use_guess, R, cn_f);
     hipStream_t s = P->stream;
     const Layout &lay = P->lay;
     const int n = lay.lev[0].n;

@@ -1,0 +1,78 @@
+"""Whole solves of 64^2 and 32^2 grids in one launch against the same solves in
+separate launches (which run while launches are timed): the same iterate bit
+for bit on non-singular problems, and its history (two orders of summing at
+most 4096 squares: 1e-9 relative is far above 4096 2^-53); singular problems,
+whose means are removed at other points, to 1e-12 of the largest value; and
+the right-hand sides that end a solve."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+cc = pytest.importorskip("paper_1306_6883_amd")
+
+
+def field(v, pad=3):
+    n = v.shape[0]
+    t = torch.zeros((n + 2, n + 2 + pad), dtype=torch.float64, device="cuda")
+    t[1:n + 1, 1:n + 1] = torch.from_numpy(v).cuda()
+    return t
+
+
+def solve(n, bc, ab, fv, guess, timed, nb=2, **kw):
+    plan = cc.Plan(cc.Problem(n=n, bc=tuple(bc), alpha=ab[0], beta=ab[1], **kw))
+    if nb != 2:
+        cc.ccmg_plan_set_bottom(plan, nb)
+    if timed:
+        cc.ccmg_plan_profile(plan, True)
+    phi = field(np.full_like(fv, 7.0) if guess is None else guess)
+    return cc.ccmg_solve(plan, field(fv), phi, use_guess=guess is not None), phi.cpu().numpy()
+
+
+@pytest.mark.parametrize("nb", [2, 4, 8])
+@pytest.mark.parametrize("bc,ab", [("DDDD", (0.0, -1.0)), ("NDPP", (0.0, -1.0)), ("PPND", (1.0, 2e-4)),
+                                   ("NNNN", (1.0, 2e-4)), ("PPPP", (0.0, -1.0))])
+@pytest.mark.parametrize("n", [32, 64])
+def test_one_launch_matches_separate_launches(n, bc, ab, nb):
+    print(f"solo n={n} bc={bc} ab={ab} nb={nb}", flush=True)
+    fv = np.random.default_rng(51).standard_normal((n, n))
+    fv -= fv.mean()
+    singular = ab[0] == 0.0 and "D" not in bc
+    for guess in (None, W.fourier_modes(n, seed=3, count=8, kmax=4) * 1e-3):
+        r, phi = solve(n, bc, ab, fv, guess, False, nb)
+        s, ref = solve(n, bc, ab, fv, guess, True, nb)
+        assert r.status == s.status == cc.OK and r.cycles == s.cycles
+        # (two digits above the residual's rounding floor, where the bits of the iterate decide)
+        h, hr = np.array(r.history), np.array(s.history)
+        np.testing.assert_allclose(h[hr > 1e-9], hr[hr > 1e-9], rtol=1e-9 if not singular else 1e-6)
+        if singular:
+            assert np.abs(phi - ref).max() <= 1e-12 * np.abs(ref).max()
+        else:
+            assert np.array_equal(phi, ref)
+
+
+@pytest.mark.parametrize("n", [32, 64])
+def test_ends_without_a_cycle(n):
+    fv = W.sine_noise(n, seed=1)
+    # a converged guess comes back unchanged
+    r, phi = solve(n, "DDDD", (0.0, -1.0), fv, None, False)
+    again, phi2 = solve(n, "DDDD", (0.0, -1.0), fv, phi[1:n + 1, 1:n + 1], False)
+    assert again.status == cc.OK and again.cycles == 0 and np.array_equal(phi2[:, :n + 2], phi[:, :n + 2])
+    # zero right-hand side, guess ignored
+    z, phi3 = solve(n, "DDDD", (0.0, -1.0), np.zeros((n, n)), phi[1:n + 1, 1:n + 1], False)
+    assert z.status == cc.OK and z.cycles == 0 and not phi3[:, :n + 2].any()
+    # tolerance out of reach
+    m, _ = solve(n, "DDDD", (0.0, -1.0), fv, None, False, max_cycles=2)
+    assert m.status == cc.NOT_CONVERGED and m.cycles == 2 and len(m.history) == 3
+    for bad, status in ((np.ones((n, n)), cc.EINCOMPAT), (np.where(fv > 0, np.inf, fv), cc.ENONFINITE)):
+        with pytest.raises(cc.CcmgError) as e:
+            solve(n, "PPPP", (0.0, -1.0), bad, None, False)
+        assert e.value.status == status
+    g = np.zeros((n, n))
+    g[2, 3] = np.nan
+    with pytest.raises(cc.CcmgError) as e:
+        solve(n, "DDDD", (0.0, -1.0), fv, g, False)
+    assert e.value.status == cc.ENONFINITE
