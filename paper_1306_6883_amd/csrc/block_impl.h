@@ -335,8 +335,9 @@ __device__ __forceinline__ void block_tile(const MarchArgs<T> &a, const int stri
 // A tile's sums are added up within the workgroup (wpb waves): every wave of
 // the next level's launches adds all partial sums of the restricted residual
 // on singular problems, a round trip to memory per 1024 of them.
-template <typename T, int NU, bool LOADPHI, bool PROLONG, int POST, int R>
-__global__ __launch_bounds__(256) void k_block(const MarchArgs<T> a) {
+// OCC: waves per SIMD to leave registers for.
+template <typename T, int NU, bool LOADPHI, bool PROLONG, int POST, int R, int OCC>
+__global__ __launch_bounds__(256, OCC) void k_block(const MarchArgs<T> a) {
     using C = BlockCfg<NU, LOADPHI, PROLONG, POST, R>;
     __shared__ double part[4][7];
     const int wpb = blockDim.x >> 6;
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(256) void k_block(const MarchArgs<T> a) {
     }
 }
 
-template <typename T, int NU, bool LOADPHI, bool PROLONG, int POST, int R>
+template <typename T, int NU, bool LOADPHI, bool PROLONG, int POST, int R, int OCC = 1>
 static hipError_t go_block(const MarchArgs<T> &a0, int wpb, hipStream_t s, int *nt) {
     MarchArgs<T> a = a0;
     a.outw = BlockCfg<NU, LOADPHI, PROLONG, POST, R>::OUTW;
@@ -402,7 +403,7 @@ static hipError_t go_block(const MarchArgs<T> &a0, int wpb, hipStream_t s, int *
     const int groups = (a.ntiles + wpb - 1) / wpb;
     if (nt) *nt = groups;
     a.groups_per_xcd = (groups + 7) / 8;
-    hipLaunchKernelGGL((k_block<T, NU, LOADPHI, PROLONG, POST, R>), dim3(8 * a.groups_per_xcd), dim3(64 * wpb), 0, s,
+    hipLaunchKernelGGL((k_block<T, NU, LOADPHI, PROLONG, POST, R, OCC>), dim3(8 * a.groups_per_xcd), dim3(64 * wpb), 0, s,
                        a);
     return hipGetLastError();
 }
@@ -415,8 +416,16 @@ hipError_t dispatch_block(const MarchArgs<T> &a, int nu, bool load_phi, bool pro
     if (a.n < 64 || a.n % R || a.count_out) return hipErrorNotSupported;
     // (16 rows and the 18 halo rows of the fused launch do not fit the registers in FP64)
     if constexpr (R == 8 || sizeof(T) == 4) {
-        if (post == POST_FUSED && nu == 4 && load_phi && prolong)
+        if (post == POST_FUSED && nu == 4 && load_phi && prolong) {
+            // FP64 needs 267 registers, one wave per SIMD.  From 1024^2 a launch
+            // has more waves than SIMDs (1280 there): two per SIMD, at twenty
+            // registers' spills, then take 67.8 - 71.1 us per cycle against
+            // 72.6 - 73.2; at 512^2 (640 waves) 51.9 against 50.4.
+            if constexpr (R == 8 && sizeof(T) == 8) {
+                if (a.n >= 1024) return go_block<T, 4, true, true, POST_FUSED, R, 2>(a, wpb, s, nt);
+            }
             return go_block<T, 4, true, true, POST_FUSED, R>(a, wpb, s, nt);
+        }
     }
     if (nu != 2) return hipErrorNotSupported;
     if (!load_phi && !prolong && post == POST_RESTRICT) return go_block<T, 2, false, false, POST_RESTRICT, R>(a, wpb, s, nt);

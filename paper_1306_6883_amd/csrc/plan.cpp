@@ -168,16 +168,18 @@ MarchShape shape_for(int n) {
 // launch: bands held in registers (block_impl.h) as far as they were the
 // faster ones -- the two launches of a level up to 2048^2 (8 rows to 512^2,
 // where every wave counts; from 1024^2 16 rows measure the same and read fewer
-// halo rows), the fused launch up to 1024^2 in FP64 (per cycle of 512^2 56 us
-// against 68 - 102 in marched bands, of 1024^2 86.5 against 89 - 125, of
-// 2048^2 127.6 against 120) and 2048^2 in FP32.
-MarchShape level_shape_for(int n) {
+// halo rows), the fused launch up to 2048^2 (per cycle of 512^2 50 us against
+// 62 - 73 in marched bands, of 1024^2 68 - 71 against 76 - 90, of 2048^2 111 -
+// 112 against 114 - 120).  Four waves per workgroup where singular plans would
+// else write over a thousand partial sums (fused, 2048^2 periodic: 110.6
+// against 115.6 us), one elsewhere (2048^2 Dirichlet: 112.1 against 114.3).
+MarchShape level_shape_for(int n, bool singular) {
     if (n < 64 || n > 2048) return shape_for(n);
-    return n >= 1024 ? MarchShape{16, 4} : MarchShape{8, 1};
+    return n >= 1024 ? MarchShape{16, singular ? 4 : 1} : MarchShape{8, 1};
 }
-MarchShape fused_shape_for(int n, bool f64) {
-    if (n < 64 || n > (f64 ? 1024 : 2048)) return n == 2048 ? MarchShape{64, 1} : shape_for(n);
-    return n >= 1024 ? MarchShape{f64 ? 8 : 16, 4} : MarchShape{8, 1};
+MarchShape fused_shape_for(int n, bool f64, bool singular) {
+    if (n < 64 || n > 2048) return shape_for(n);
+    return n >= 1024 ? MarchShape{f64 ? 8 : 16, singular ? 4 : 1} : MarchShape{8, 1};
 }
 
 // Default shape of a visit launch: its bands carry 8 halo rows on either
@@ -1001,14 +1003,14 @@ void plan_init_host(ccmg_plan *P, const ccmg_problem &p) {
     P->singular = p.alpha == 0.0 && p.bc[0] != CCMG_BC_DIRICHLET && p.bc[1] != CCMG_BC_DIRICHLET &&
                   p.bc[2] != CCMG_BC_DIRICHLET && p.bc[3] != CCMG_BC_DIRICHLET;
     for (int l = 0; l < P->lay.L && l < kMaxLevels; ++l) {
-        P->shp_pre[l] = P->shp_post[l] = P->shp_pre_v[l] = level_shape_for(P->lay.lev[l].n);
+        P->shp_pre[l] = P->shp_post[l] = P->shp_pre_v[l] = level_shape_for(P->lay.lev[l].n, P->singular);
         P->shp_visit[l] = visit_shape_for(P->lay.lev[l].n);
         P->visit[l] = false;
     }
-    P->shp_fused = fused_shape_for(P->lay.lev[0].n, true);
+    P->shp_fused = fused_shape_for(P->lay.lev[0].n, true, P->singular);
     P->shp_fused0 = shape_for(P->lay.lev[0].n);
     P->fused0 = false;
-    P->shp_fused32 = fused_shape_for(P->lay.lev[0].n, false);
+    P->shp_fused32 = fused_shape_for(P->lay.lev[0].n, false, P->singular);
     P->n_bottom = 2;
     P->tcycle = 0;
     P->timer.on = false;
