@@ -22,6 +22,7 @@
 // there; on a y side the rows y = 0 and y = n - 1 sit at fixed places of a
 // band or of its halo (R divides n), so only those need a select.
 #pragma once
+#include "cycle_end.h"
 #include "march_impl.h"
 
 #pragma clang fp contract(on)
@@ -340,6 +341,14 @@ template <typename T, int NU, bool LOADPHI, bool PROLONG, int POST, int R, int O
 __global__ __launch_bounds__(256, OCC) void k_block(const MarchArgs<T> a) {
     using C = BlockCfg<NU, LOADPHI, PROLONG, POST, R>;
     __shared__ double part[4][7];
+    if constexpr (!LOADPHI && !PROLONG && POST == POST_RESTRICT) {
+        // the last workgroup: the end of the cycle before, which nothing else in
+        // this launch reads (a launch of its own took 4 us of every cycle)
+        if (a.end.partial && blockIdx.x == gridDim.x - 1) {
+            if (threadIdx.x < 64) cycle_end_one_wave(a.end);
+            return;
+        }
+    }
     const int wpb = blockDim.x >> 6;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // XCD-aware order, as in k_march: each XCD gets a contiguous run of tiles
@@ -403,8 +412,9 @@ static hipError_t go_block(const MarchArgs<T> &a0, int wpb, hipStream_t s, int *
     const int groups = (a.ntiles + wpb - 1) / wpb;
     if (nt) *nt = groups;
     a.groups_per_xcd = (groups + 7) / 8;
-    hipLaunchKernelGGL((k_block<T, NU, LOADPHI, PROLONG, POST, R, OCC>), dim3(8 * a.groups_per_xcd), dim3(64 * wpb), 0, s,
-                       a);
+    const int extra = !LOADPHI && !PROLONG && POST == POST_RESTRICT && a.end.partial ? 1 : 0;
+    hipLaunchKernelGGL((k_block<T, NU, LOADPHI, PROLONG, POST, R, OCC>), dim3(8 * a.groups_per_xcd + extra),
+                       dim3(64 * wpb), 0, s, a);
     return hipGetLastError();
 }
 
@@ -413,7 +423,8 @@ static hipError_t go_block(const MarchArgs<T> &a0, int wpb, hipStream_t s, int *
 template <typename T, int R>
 hipError_t dispatch_block(const MarchArgs<T> &a, int nu, bool load_phi, bool prolong, int post, int wpb,
                           hipStream_t s, int *nt) {
-    if (a.n < 64 || a.n % R || a.count_out) return hipErrorNotSupported;
+    if (a.count_out || !block_runs(a.n, nu, load_phi, prolong, post, MarchShape{R, 1}, sizeof(T) == 8))
+        return hipErrorNotSupported;
     // (16 rows and the 18 halo rows of the fused launch do not fit the registers in FP64)
     if constexpr (R == 8 || sizeof(T) == 4) {
         if (post == POST_FUSED && nu == 4 && load_phi && prolong) {

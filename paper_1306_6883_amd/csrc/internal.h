@@ -37,6 +37,20 @@ enum Post {
                         // (not loaded)
 };
 
+// End of a cycle: the (sum r^2, sum phi) pairs of `count` tiles, added in a
+// fixed order, give *rho_out (and *host_rho, host-mapped, if set) = sqrt(sum
+// r^2) / sqrt(*f2), *phi_mean = sum phi / n^2 (singular) or 0, and *done = 1 if
+// that is within rtol or not finite; nothing if *done (if set) is already 1.
+struct CycleEnd {
+    const double *partial;
+    int count, n, singular;
+    const double *f2;
+    double rtol;
+    double *rho_out, *phi_mean;
+    int *done;
+    double *host_rho;
+};
+
 // Arguments of one row-march launch over one grid level (see march.hip).
 template <typename T>
 struct MarchArgs {
@@ -94,6 +108,9 @@ struct MarchArgs {
     T *cn_f;
     int pcnf;
     T cn_beta;
+    // POST_RESTRICT from zero in bands held in registers (see block_runs): one
+    // more workgroup files this end of the cycle before (partial: null if none)
+    CycleEnd end;
 };
 
 // One unit of work of a batched launch: tile `tile` of level descriptor `desc`.
@@ -134,6 +151,14 @@ hipError_t launch_march(const MarchArgs<T> &a, int nu, bool load_phi, bool prolo
 template <typename T, int R>
 hipError_t dispatch_block(const MarchArgs<T> &a, int nu, bool load_phi, bool prolong, int post, int wpb,
                           hipStream_t s, int *nt);
+// Whether a launch of that shape runs so.
+inline bool block_runs(int n, int nu, bool load_phi, bool prolong, int post, MarchShape sh, bool f64) {
+    const int r = sh.ty == 0 ? 8 : sh.ty;
+    if ((r != 8 && r != 16) || n < 64 || n % r) return false;
+    if (post == POST_FUSED) return nu == 4 && load_phi && prolong && (r == 8 || !f64);
+    if (nu != 2) return false;
+    return prolong ? load_phi && (post == POST_NONE || post == POST_NORM) : post == POST_RESTRICT;
+}
 // The fused finest-level launch (POST_FUSED; march_f64_fused.hip).
 hipError_t dispatch_fused(const MarchArgs<double> &a, MarchShape sh, hipStream_t s, int *nt);
 hipError_t dispatch_fused(const MarchArgs<float> &a, MarchShape sh, hipStream_t s, int *nt);
@@ -227,11 +252,6 @@ void coarse_fill_consts(CoarseArgs<T> &a);
 // util.hip
 hipError_t launch_fill_ghosts_f64(double *a, long pitch, int n, const int bc[4], const double *shift,
                                   hipStream_t s);
-// End of a cycle: sum the (sum r^2, sum phi) tile pairs in a fixed order, then
-//   *rho_out = sqrt(sum r^2) / sqrt(*f2),  *phi_mean = sum phi / n^2 (singular) or 0,
-//   *done = 1 if rho <= rtol or rho is not finite.
-// Does nothing if *done is already set.  One workgroup.
-// host_rho (optional): host-mapped address that also receives rho.
 // Side data (bcdata.hip): per side its type and a device array of n values
 // (nullptr: homogeneous).
 struct BcData {
@@ -251,9 +271,8 @@ hipError_t launch_subtract_gradient(const double *phi, double *u, double *v, lon
 // Crank-Nicolson right-hand side f = phi + beta Lap phi on valid cells (cn.hip).
 hipError_t launch_cn_rhs(const double *phi, long pp, double *f, long pf, int n, const int bc[4], double beta,
                          double h, hipStream_t s);
-hipError_t launch_cycle_end(const double *partial, int count, int n, int singular, const double *f2,
-                            double rtol, double *rho_out, double *phi_mean, int *done, double *host_rho,
-                            hipStream_t s);
+// One workgroup.
+hipError_t launch_cycle_end(const CycleEnd &c, hipStream_t s);
 // Statistics of f (sum, sum |f|, sum f^2, non-finite count) -> out4; `blocks` partials.
 hipError_t launch_fstats(const double *f, long pitch, int n, double *partial, int blocks, double *out4,
                          hipStream_t s);

@@ -233,6 +233,12 @@ struct ccmg_plan {
     int opt_visit = 1;           // coarse levels as visits: 0 never, 1 where autotuned, 2 wherever they apply
     int n_bottom = 2;  // 4 or 8: exact solve on that level (ccmg_plan_set_bottom)
     int tcycle = 0;    // cycle being enqueued by the solve loop (tags timed launches)
+    // a fused cycle's end left to the next cycle's first coarse launch (pend_on:
+    // there is one; pend_may: this solve's coarse launches can take it) and the
+    // event to record after it
+    CycleEnd pend{};
+    bool pend_on = false, pend_may = false;
+    hipEvent_t pend_ev = nullptr;
     double *hrho = nullptr;   // host-mapped: relative residual of each cycle
     double *drho = nullptr;   // ... its device address
     Layout lay;
@@ -428,6 +434,36 @@ void coarse_consts(const ccmg_plan *P, int l, CoarseArgs<T> &c) {
     c.ainv = P->n_bottom >= 4 ? P->at<double>(P->lay.ainv) : nullptr;
 }
 
+// End of a cycle filed in history slot `slot`: residual norm of the `count`
+// pairs in normpart.  done / host: whether the stop test sets the done flag
+// and the host-mapped history.
+CycleEnd cycle_end_args(ccmg_plan *P, int count, int slot, bool singular, bool done, bool host) {
+    CycleEnd c{};
+    c.partial = P->at<double>(P->lay.normpart);
+    c.count = count;
+    c.n = P->lay.lev[0].n;
+    c.singular = singular ? 1 : 0;
+    c.f2 = P->scal() + S_F2;
+    c.rtol = P->p.rtol;
+    c.rho_out = P->hist() + slot;
+    c.phi_mean = P->scal() + S_PHIMEAN;
+    c.done = done ? P->done() : nullptr;
+    c.host_rho = host ? P->drho + slot : nullptr;
+    return c;
+}
+hipError_t end_cycle(ccmg_plan *P, int count, int slot) {
+    return launch_cycle_end(cycle_end_args(P, count, slot, P->singular, true, true), P->stream);
+}
+// A fused cycle's end may be left to the next cycle's first coarse launch
+// (enqueue_cycle); flushed as a launch of its own when the host wants it first.
+hipError_t flush_pending_end(ccmg_plan *P) {
+    if (!P->pend_on) return hipSuccess;
+    P->pend_on = false;
+    hipError_t e = launch_cycle_end(P->pend, P->stream);
+    if (e == hipSuccess) e = hipEventRecord(P->pend_ev, P->stream);
+    return e;
+}
+
 // Enqueue one V-cycle in precision T.  Returns in *norm_tiles the tile count of
 // the launch that wrote per-tile norm partials (POST_NORM / POST_IR), else 0.
 template <typename T>
@@ -529,8 +565,18 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
             const double nn = (double)lay.lev[l].n * lay.lev[l].n;
             const int ti = l == 0 ? P->tstart(f64 ? 0 : 2, sizeof(T) * nn * ((zero ? 2.0 : 3.0) + (last ? 0.25 : 0.0)))
                                   : -1;
+            const bool ends = P->pend_on && io.coarse_only && l == 1;  // (one launch: nu1 = 2)
+            if (ends) {
+                // the end of the cycle before may set the done flag, so this
+                // launch does not look at it: on a cycle queued past the last
+                // one it only rewrites coarse buffers
+                a.end = P->pend;
+                a.skip = nullptr;
+                P->pend_on = false;
+            }
             e = launch_march<T>(a, chain[i], !zero, false, post, sh, s, &nt);
             P->tstop(ti);
+            if (ends && e == hipSuccess) e = hipEventRecord(P->pend_ev, s);
             if (e != hipSuccess) return e;
             if (last) fpart_count[l + 1] = nt;
             if (!vis) std::swap(cur[l], other[l]);
@@ -689,9 +735,7 @@ hipError_t enqueue_vcycle64(ccmg_plan *P, const double *f0, long pf0, double *ph
     int nt = 0;
     hipError_t e = enqueue_cycle<double>(P, io, &nt);
     if (e == hipSuccess && with_norm)
-        e = launch_cycle_end(P->at<double>(P->lay.normpart), nt, P->lay.lev[0].n, P->singular ? 1 : 0,
-                             P->scal() + S_F2, P->p.rtol, P->hist() + slot, P->scal() + S_PHIMEAN, P->done(),
-                             P->drho + slot, P->stream);
+        e = end_cycle(P, nt, slot);
     return e;
 }
 
@@ -769,9 +813,7 @@ hipError_t enqueue_fmg(ccmg_plan *P, const double *f0, long pf0, double *phi0, l
                                      shape_for(lay.lev[0].n), s, &nt);
         }
         if (e == hipSuccess && norm_slot >= 0)
-            return launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, P->singular ? 1 : 0,
-                                    P->scal() + S_F2, P->p.rtol, P->hist() + norm_slot, P->scal() + S_PHIMEAN,
-                                    P->done(), P->drho + norm_slot, s);
+            return end_cycle(P, nt, norm_slot);
         for (int k = 0; k < ncyc && e == hipSuccess; ++k)
             e = enqueue_vcycle64(P, f0, pf0, phi0, pp0, false, nullptr, false, 0);
         return e;
@@ -789,9 +831,7 @@ hipError_t enqueue_fmg(ccmg_plan *P, const double *f0, long pf0, double *phi0, l
         a.partial = P->at<double>(lay.normpart);
         e = launch_march<double>(a, 0, true, false, POST_NORM, shape_for(lay.lev[0].n), s, &nt);
         if (e == hipSuccess)
-            e = launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, P->singular ? 1 : 0,
-                                 P->scal() + S_F2, P->p.rtol, P->hist() + norm_slot, P->scal() + S_PHIMEAN,
-                                 P->done(), P->drho + norm_slot, s);
+            e = end_cycle(P, nt, norm_slot);
     }
     return e;
 }
@@ -833,9 +873,7 @@ hipError_t enqueue_mixed_start(ccmg_plan *P, const double *d_f, long pf, MixedSt
     st.r_tiles = nt;
     if (e == hipSuccess && stats_host) e = launch_reduce4(P->at<double>(P->lay.fstats), nt, P->scal() + S_FSUM, P->stream);
     if (e == hipSuccess)
-        e = launch_cycle_end(P->at<double>(P->lay.normpart), nt, P->lay.lev[0].n, P->singular ? 1 : 0,
-                             P->scal() + S_F2, P->p.rtol, P->hist() + slot, P->scal() + S_PHIMEAN, P->done(),
-                             P->drho + slot, P->stream);
+        e = end_cycle(P, nt, slot);
     if (e == hipSuccess && stats_host)
         e = hipMemcpyAsync(stats_host, P->scal(), sizeof(double) * kScal, hipMemcpyDeviceToHost, P->stream);
     return e;
@@ -879,9 +917,7 @@ hipError_t enqueue_mixed_step(ccmg_plan *P, const double *d_f, long pf, MixedSta
     std::swap(st.s3, st.s3o);
     st.r_tiles = nt;
     st.q_zero = false;
-    return launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, P->singular ? 1 : 0, P->scal() + S_F2,
-                            P->p.rtol, P->hist() + slot, P->scal() + S_PHIMEAN, skip ? P->done() : nullptr,
-                            skip ? P->drho + slot : nullptr, P->stream);
+    return launch_cycle_end(cycle_end_args(P, nt, slot, P->singular, skip != nullptr, skip != nullptr), P->stream);
 }
 
 // A refinement step with m >= 2 FP32 V-cycles for A e = r32 (e from zero):
@@ -990,9 +1026,7 @@ hipError_t enqueue_mixed_step_inner(ccmg_plan *P, const double *d_f, long pf, Mi
     std::swap(st.s3, st.s3o);
     st.r_tiles = nt;
     st.q_zero = false;
-    return launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, P->singular ? 1 : 0, P->scal() + S_F2,
-                            P->p.rtol, P->hist() + slot, P->scal() + S_PHIMEAN, skip ? P->done() : nullptr,
-                            skip ? P->drho + slot : nullptr, s);
+    return launch_cycle_end(cycle_end_args(P, nt, slot, P->singular, skip != nullptr, skip != nullptr), P->stream);
 }
 
 // Host-side state of a plan for problem p (validated): layout, side type
@@ -1988,8 +2022,7 @@ hipError_t enqueue_fused_cycle(ccmg_plan *P, FusedCtx &cx, const double *d_f, lo
                 // the guess's residual norm -> history entry 0 (a guess within
                 // the tolerance sets the done flag: the rest of the cycle does nothing)
                 if (e == hipSuccess && first_norm)
-                    e = launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, 0, P->scal() + S_F2,
-                                         P->p.rtol, P->hist(), P->scal() + S_PHIMEAN, P->done(), P->drho, s);
+                    e = launch_cycle_end(cycle_end_args(P, nt, 0, false, true, true), P->stream);
                 if (e == hipSuccess)
                     e = hipMemcpyAsync(cx.stats_host, P->scal(), sizeof(double) * kScal, hipMemcpyDeviceToHost, s);
                 cx.first_stats = false;
@@ -2067,8 +2100,12 @@ hipError_t enqueue_fused_cycle(ccmg_plan *P, FusedCtx &cx, const double *d_f, lo
         cx.next = Buf<double>{nullptr, 0};
         cx.cur = A;
     }
-    return launch_cycle_end(P->at<double>(lay.normpart), nt, lay.lev[0].n, P->singular ? 1 : 0, P->scal() + S_F2,
-                            P->p.rtol, P->hist() + slot, P->scal() + S_PHIMEAN, P->done(), P->drho + slot, s);
+    if (P->pend_may) {
+        P->pend = cycle_end_args(P, nt, slot, P->singular, true, true);
+        P->pend_on = true;
+        return hipSuccess;
+    }
+    return end_cycle(P, nt, slot);
 }
 }  // namespace
 
@@ -2255,8 +2292,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
         int nt = 0;
         e = launch_march<double>(a, 0, true, false, POST_NORM, shape_for(n), s, &nt);
         if (e == hipSuccess)
-            e = launch_cycle_end(P->at<double>(lay.normpart), nt, n, P->singular ? 1 : 0, scal + S_F2,
-                                 P->p.rtol, P->hist(), scal + S_PHIMEAN, P->done(), P->drho, s);
+            e = end_cycle(P, nt, 0);
     }
     if (e == hipSuccess && !late)
         e = hipMemcpyAsync(P->hpin + CCMG_HISTORY, scal, sizeof(double) * kScal, hipMemcpyDeviceToHost, s);
@@ -2318,6 +2354,14 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
     fx.stats_host = P->hpin + CCMG_HISTORY;
     fx.allow_recompute = P->p.max_cycles >= 2 && (P->opt_visit == 2 || (P->opt_visit == 1 && P->fused0));
     std::vector<FusedCtx> fafter(P->p.max_cycles + 2, fx);
+    // The end of a fused cycle (one workgroup, 4 us) runs inside the next
+    // cycle's first coarse launch where that is one of bands held in registers.
+    // From 256^2: the host reads the residual a launch later, and below that
+    // what is left of the cycle is shorter than queueing the next one.
+    P->pend_on = false;
+    P->pend_may = fused && n >= 256 &&
+                  block_runs(n / 2, 2, false, false, POST_RESTRICT, visit_level(P, 1) ? P->shp_pre_v[1] : P->shp_pre[1],
+                             true);
     if (rho0 <= P->p.rtol) {
         status = CCMG_OK;
     } else if (P->p.max_cycles > 0) {
@@ -2401,7 +2445,8 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
             } else {
                 x = enqueue_vcycle64(P, d_f, pitch, d_phi, pitch, k == 1 && !guess, shift, true, k);
             }
-            if (x == hipSuccess) x = hipEventRecord(cycle_event(k), s);
+            if (P->pend_on) P->pend_ev = cycle_event(k);
+            else if (x == hipSuccess) x = hipEventRecord(cycle_event(k), s);
             return x;
         };
         // Cycle k+1 is queued before cycle k's residual is read, so the GPU
@@ -2422,6 +2467,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
                     queued = k + 1;
                 }
             }
+            if (e == hipSuccess && queued == k) e = flush_pending_end(P);
             if (e != hipSuccess) break;
             e = hipEventSynchronize(cycle_event(k));
             if (e != hipSuccess) break;
@@ -2466,6 +2512,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
                 queued = k + 1;
             }
         }
+        P->pend_on = false;  // (of a cycle queued past the last one)
         if (e != hipSuccess) return R->status = CCMG_EHIP;
         if (fused && cycles > 0) {
             const FusedCtx &fc = fafter[cycles];
@@ -2489,8 +2536,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
                 int nt = 0;
                 if (e == hipSuccess) e = launch_march<double>(a, 0, true, false, POST_NORM, shape_for(n), s, &nt);
                 if (e == hipSuccess)
-                    e = launch_cycle_end(P->at<double>(lay.normpart), nt, n, P->singular ? 1 : 0, scal + S_F2,
-                                         P->p.rtol, P->hist() + slot, scal + S_PHIMEAN, P->done(), P->drho + slot, s);
+                    e = end_cycle(P, nt, slot);
                 if (e == hipSuccess) e = hipStreamSynchronize(s);
                 if (e == hipSuccess) {
                     rho = P->hrho[slot];

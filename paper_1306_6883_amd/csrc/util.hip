@@ -1,6 +1,7 @@
 // util.hip -- small kernels around the V-cycle: ghost cells of the output,
 // statistics of the right-hand side, and the fixed-order reductions that turn
 // per-tile partial sums into the residual norm and the mean of phi.
+#include "cycle_end.h"
 #include "internal.h"
 
 namespace ccmg {
@@ -60,44 +61,24 @@ hipError_t launch_fill_ghosts_f64(double *a, long pitch, int n, const int bc[4],
     return hipGetLastError();
 }
 
-// End of a cycle (see internal.h).
-__global__ __launch_bounds__(kRed) void k_cycle_end(const double *p, int count, int n, int singular,
-                                                    const double *f2, double rtol, double *rho_out,
-                                                    double *phi_mean, int *done, double *host_rho) {
-    __shared__ double red[4];
-    if (done && *done) return;  // uniform
-    double s0 = 0.0, s1 = 0.0;
-    int i = threadIdx.x;
-    for (; i + 3 * kRed < count; i += 4 * kRed) {  // four pairs in flight, added in order
-        double2 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const double2 *>(p + 2 * (i + k * kRed));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            s0 += v[k].x;
-            s1 += v[k].y;
-        }
+// End of a cycle as a launch of its own.
+__global__ __launch_bounds__(kRed) void k_cycle_end(const CycleEnd c) {
+    __shared__ double red[2][4];
+    if (c.done && *c.done) return;  // uniform
+    const double2 v = cycle_end_thread(c.partial, c.count, threadIdx.x);
+    const double s0 = cycle_end_wave(v.x), s1 = cycle_end_wave(v.y);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = s0;
+        red[1][threadIdx.x >> 6] = s1;
     }
-    for (; i < count; i += kRed) {
-        s0 += p[2 * i];
-        s1 += p[2 * i + 1];
-    }
-    s0 = block_sum256(s0, red);
-    s1 = block_sum256(s1, red);
-    if (threadIdx.x == 0) {
-        const double rho = sqrt(s0) / sqrt(*f2);
-        *rho_out = rho;
-        if (host_rho) *host_rho = rho;  // host-mapped: read by the host after the cycle's event
-        *phi_mean = singular ? s1 / ((double)n * (double)n) : 0.0;
-        if (done && (rho <= rtol || !isfinite(rho))) *done = 1;
-    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        cycle_end_file(c, ((red[0][0] + red[0][1]) + red[0][2]) + red[0][3],
+                       ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3]);
 }
 
-hipError_t launch_cycle_end(const double *partial, int count, int n, int singular, const double *f2,
-                            double rtol, double *rho_out, double *phi_mean, int *done, double *host_rho,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_cycle_end, dim3(1), dim3(kRed), 0, s, partial, count, n, singular, f2, rtol,
-                       rho_out, phi_mean, done, host_rho);
+hipError_t launch_cycle_end(const CycleEnd &c, hipStream_t s) {
+    hipLaunchKernelGGL(k_cycle_end, dim3(1), dim3(kRed), 0, s, c);
     return hipGetLastError();
 }
 
