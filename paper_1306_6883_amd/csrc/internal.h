@@ -280,6 +280,7 @@ hipError_t launch_fstats(const double *f, long pitch, int n, double *partial, in
 hipError_t launch_fstats_restrict(const double *f, long pitch, int n, double *partial, int blocks, double *out4,
                                   double *coarse, long pc, hipStream_t s);
 hipError_t launch_set(double *p, int count, double v, hipStream_t s);
+hipError_t launch_reset(int *done, double *scal, int count, hipStream_t s);
 // out4[q] = sum over i < count of partial[4 i + q], in a fixed order (one workgroup).
 hipError_t launch_reduce4(const double *partial, int count, double *out4, hipStream_t s);
 hipError_t launch_set_int(int *p, int count, int v, hipStream_t s);

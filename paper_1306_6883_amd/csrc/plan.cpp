@@ -2118,8 +2118,7 @@ int ccmg_vcycle(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t pitch)
         return hip_status(enqueue_vcycle64(P, d_f, pitch, d_phi, pitch, false, nullptr, false, 0));
     // MIXED: one refinement step in place
     MixedState st = mixed_state(P, d_phi, pitch, false);
-    hipError_t e = launch_set_int(P->done(), 1, 0, P->stream);
-    if (e == hipSuccess) e = launch_set(P->scal(), kScal, 0.0, P->stream);
+    hipError_t e = launch_reset(P->done(), P->scal(), kScal, P->stream);
     if (e == hipSuccess) e = launch_fstats(d_f, pitch, P->lay.lev[0].n, P->at<double>(P->lay.fstats), kStatBlocks,
                                            P->scal() + S_FSUM, P->stream);
     if (e == hipSuccess) e = enqueue_mixed_start(P, d_f, pitch, st, true, 0);
@@ -2242,8 +2241,7 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
     hipError_t e = hipEventRecord(P->ev_t0, s);
 
     // statistics of f, reset of the flags, and the starting residual
-    if (e == hipSuccess) e = launch_set_int(P->done(), 1, 0, s);
-    if (e == hipSuccess) e = launch_set(scal, kScal, 0.0, s);
+    if (e == hipSuccess) e = launch_reset(P->done(), scal, kScal, s);
     // full multigrid start: f's statistics and its restriction to level 1 from one read
     const bool fmg_f1 = P->opt_fmg > 0 && !use_guess && !mixed && lay.lt >= 1;
     // FP64 solves from zero with the fused finest launch take f's statistics

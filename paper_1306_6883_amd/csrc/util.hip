@@ -227,6 +227,17 @@ hipError_t launch_set(double *p, int count, double v, hipStream_t s) {
     hipLaunchKernelGGL(k_set, dim3(1), dim3(64), 0, s, p, count, v);
     return hipGetLastError();
 }
+// Start of a solve: the done flag and the scalars (count <= 64) cleared.
+__global__ void k_reset(int *done, double *scal, int count) {
+    const int i = threadIdx.x;
+    if (i == 0) *done = 0;
+    if (i < count) scal[i] = 0.0;
+}
+hipError_t launch_reset(int *done, double *scal, int count, hipStream_t s) {
+    if (count > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, done, scal, count);
+    return hipGetLastError();
+}
 __global__ void k_set_int(int *p, int count, int v) {
     const int i = threadIdx.x;
     if (i < count) p[i] = v;
