@@ -36,12 +36,21 @@ namespace {
 constexpr int kMaxLevelsB = 16;
 constexpr int kStatBlocksB = 64;
 constexpr int kMinTyB = 8;
-constexpr int kMinOutwB = 112;
+constexpr int kMinOutwB = march_outw(4, false, true);  // the narrowest strips (POST_IR0)
 constexpr int kMaxWaves = 4096;
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 long pitch_of(int n) { return (long)((n + 2 + 31) & ~31); }
 int tiles_max(int n) { return ((n + kMinOutwB - 1) / kMinOutwB) * ((n + kMinTyB - 1) / kMinTyB); }
+// Levels of this many cells per side on recompute the iterate the way down left
+// instead of storing and reading it back (8 of the 46 or 22 B/cell): the finest
+// level's last launch from 256 on, a coarser level's visit from 512 on.  In a
+// step of 512 problems: 1024^2 907 -> 807 us and 225 -> 153 for its way down;
+// 512^2 238 -> 206 and 137 -> 97, coarser 512^2 95 -> 69 and 97 -> 74; 256^2
+// 69 -> 62 and 62 -> 51.  Below, the fields come from the caches and the 8 more
+// halo rows cost what they save (128^2 33 -> 36 and 28 -> 26, 64^2 19 -> 27).
+constexpr int kRecomputeFinest = 256, kRecomputeCoarse = 512;
+bool recomputes(int n, int l) { return (n >> l) >= (l == 0 ? kRecomputeFinest : kRecomputeCoarse); }
 int log2i(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 // Per-problem workspace (FP32 levels, FP64 second iterate, partial sums).
@@ -93,7 +102,7 @@ ProbLay prob_layout(const ccmg_problem &p) {
 enum { I_DONE = 0, I_CYC = 1, I_R32CNT = 2, I_FPCNT = 4, kInts = I_FPCNT + kMaxLevelsB };
 
 // Kinds of launches in a step.
-enum Kind { K_PRE = 0, K_POSTC = 1, K_POSTF = 2, K_TAILF = 3, K_START = 4, K_START_GUESS = 5 };
+enum Kind { K_PRE = 0, K_POSTC, K_VISIT, K_POSTF, K_POSTF0, K_TAILF, K_START, K_START_GUESS };
 
 struct Launch {
     int kind = 0;
@@ -182,11 +191,6 @@ void set_tiles(MarchArgs<T> &a, int outw, int ty) {
     a.groups_per_xcd = 0;
 }
 
-int outw_of(int nu, bool prolong, bool post) {
-    const int hxc = 2 * nu + (post ? 1 : 0) + (prolong ? 2 : 0);
-    return 128 - 2 * ((hxc + 1) & ~1);
-}
-
 bool singular_of(const ccmg_problem &p) {
     if (p.alpha != 0.0) return false;
     for (int s = 0; s < 4; ++s)
@@ -249,13 +253,13 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
             if (l >= pl.lt) continue;
             MarchArgs<float> a{};
             consts_for(p, pl, l, a);
-            set_tiles(a, outw_of(2, false, true), B->ty.at(s));
+            set_tiles(a, march_outw(2, false, true), B->ty.at(s));
             a.f = l == 0 ? r_ptr(i, rin) : B->pat<float>(i, pl.lev_f[l]);
             a.pf = pl.pitch[l];
             fmean_fill(i, l, a);
             a.phi_in = B->pat<float>(i, pl.lev_a[l]);
             a.pin = pl.pitch[l];
-            a.phi_out = B->pat<float>(i, pl.lev_b[l]);
+            a.phi_out = recomputes(p.n, l) ? nullptr : B->pat<float>(i, pl.lev_b[l]);
             a.pout = pl.pitch[l];
             a.aux = B->pat<float>(i, pl.lev_f[l + 1]);
             a.paux = pl.pitch[l + 1];
@@ -272,8 +276,9 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
     std::vector<int> asc(B->sizes.rbegin(), B->sizes.rend());
     for (int s : asc) {
         HostLaunch HC, HF;
-        HC.L.kind = K_POSTC;
-        HF.L.kind = K_POSTF;
+        // (a size class is one side of the line for all its problems)
+        HC.L.kind = s >= kRecomputeCoarse ? K_VISIT : K_POSTC;
+        HF.L.kind = s >= kRecomputeFinest ? K_POSTF0 : K_POSTF;
         HC.L.size = HF.L.size = s;
         for (int i = 0; i < B->m; ++i) {
             const ccmg_problem &p = B->prob[i];
@@ -283,11 +288,14 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
             if (l >= pl.lt) continue;
             MarchArgs<float> a{};
             consts_for(p, pl, l, a);
-            set_tiles(a, outw_of(2, true, l == 0), B->ty.at(s));
+            const bool rec = recomputes(p.n, l);
+            set_tiles(a, l == 0 ? (rec ? march_outw(4, false, true) : march_outw(2, true, true))
+                                : (rec ? march_outw(4, true, false) : march_outw(2, true, false)),
+                      B->ty.at(s));
             a.f = l == 0 ? r_ptr(i, rin) : B->pat<float>(i, pl.lev_f[l]);
             a.pf = pl.pitch[l];
             fmean_fill(i, l, a);
-            a.phi_in = B->pat<float>(i, pl.lev_b[l]);
+            a.phi_in = B->pat<float>(i, pl.lev_b[l]);  // (not read where it is recomputed)
             a.pin = pl.pitch[l];
             a.phi_out = B->pat<float>(i, pl.lev_a[l]);
             a.pout = pl.pitch[l];
@@ -316,7 +324,7 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
             if (pl.lt != 0) continue;
             MarchArgs<float> a{};
             consts_for(p, pl, 0, a);
-            set_tiles(a, outw_of(0, false, true), p.n);
+            set_tiles(a, march_outw(0, false, true), p.n);
             a.f = r_ptr(i, rin);
             a.pf = pl.pitch[0];
             fmean_fill(i, 0, a);
@@ -339,7 +347,7 @@ void build_start(const ccmg_batch *B, bool guess, HostLaunch &H) {
         const ProbLay &pl = B->pl[i];
         MarchArgs<double> a{};
         consts_for(p, pl, 0, a);
-        set_tiles(a, outw_of(0, false, true), B->ty.count(p.n) ? B->ty.at(p.n) : 16);
+        set_tiles(a, march_outw(0, false, true), B->ty.count(p.n) ? B->ty.at(p.n) : 16);
         a.f = B->cf[i];
         a.pf = B->cpitch[i];
         a.phi_in = B->cphi[i];
@@ -452,6 +460,12 @@ hipError_t launch_one(ccmg_batch *B, const Launch &L) {
         case K_POSTF:
             return launch_list_variant<float, 2, true, true, POST_IR>(B->at<MarchArgs<float>>(L.desc_off), it,
                                                                     L.nitems, waves, B->stream);
+        case K_VISIT:
+            return launch_list_variant<float, 4, false, true, POST_VISIT>(B->at<MarchArgs<float>>(L.desc_off), it,
+                                                                        L.nitems, waves, B->stream);
+        case K_POSTF0:
+            return launch_list_variant<float, 4, false, true, POST_IR0>(B->at<MarchArgs<float>>(L.desc_off), it,
+                                                                      L.nitems, waves, B->stream);
         case K_TAILF:
             return launch_list_variant<float, 0, true, false, POST_IR>(B->at<MarchArgs<float>>(L.desc_off), it,
                                                                      L.nitems, waves, B->stream);
@@ -814,8 +828,8 @@ int ccmg_batch_autotune(ccmg_batch *B, const double *const *d_f, double *const *
         hipEventDestroy(e0);
         return CCMG_EHIP;
     }
-    const int cands[] = {8, 16, 32, 64};
-    const int wave_cands[] = {1024, 2048, 4096};
+    const int cands[] = {8, 16, 32, 64, 128};
+    const int wave_cands[] = {1024, 2048, 4096, 8192, 32768};
     auto time_steps = [&](float &ms) -> hipError_t {
         hipError_t x = launch_batch_fstats(B->at<BatchProb>(B->off_probs[0]), B->m, kStatBlocksB, B->stream);
         if (x == hipSuccess) x = launch_one(B, B->start);

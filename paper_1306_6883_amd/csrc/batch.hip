@@ -161,6 +161,11 @@ template hipError_t launch_list_variant<float, 2, true, true, POST_NONE>(const M
                                                                          const WorkItem *, int, int, hipStream_t);
 template hipError_t launch_list_variant<float, 2, true, true, POST_IR>(const MarchArgs<float> *, const WorkItem *,
                                                                        int, int, hipStream_t);
+template hipError_t launch_list_variant<float, 4, false, true, POST_VISIT>(const MarchArgs<float> *,
+                                                                           const WorkItem *, int, int,
+                                                                           hipStream_t);
+template hipError_t launch_list_variant<float, 4, false, true, POST_IR0>(const MarchArgs<float> *, const WorkItem *,
+                                                                       int, int, hipStream_t);
 template hipError_t launch_list_variant<float, 0, true, false, POST_IR>(const MarchArgs<float> *,
                                                                         const WorkItem *, int, int, hipStream_t);
 template hipError_t launch_list_variant<double, 0, false, false, POST_R32>(const MarchArgs<double> *,

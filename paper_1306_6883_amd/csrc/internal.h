@@ -31,6 +31,9 @@ enum Post {
     POST_FUSED0 = 8,    // (finest level, NU = 6, from zero) the first fused launch of a solve
                         // from zero: the first cycle's two pre-smoothing iterations recomputed
                         // from zero as in POST_VISIT, then everything POST_FUSED does
+    POST_IR0 = 10,      // (float launches, finest level, NU = 4, from zero) the two pre-smoothing
+                        // iterations recomputed from zero and the prolongation as in POST_VISIT,
+                        // the two post-smoothing iterations, then everything POST_IR does
     POST_CNPRE = 9      // (finest level, FP64, NU = 2, from a loaded iterate) POST_RESTRICT
                         // whose right-hand side is the Crank-Nicolson one of the loaded
                         // iterate, f = phi + cn_beta Lap phi, formed here and written to cn_f

@@ -121,16 +121,18 @@ struct Cfg {
     // VISIT: pre-smoothing stages 1 .. 4 from zero, the prolongation,
     // post-smoothing stages 5 .. 8; no residual.  FUSED0: the same four
     // stages and prolongation, then POST_FUSED's stages, norm and residual.
+    // IR0: VISIT's stages, then POST_IR's update and residual.
     static constexpr bool VISIT = POST == POST_VISIT;
     static constexpr bool FUSED0 = POST == POST_FUSED0;
-    static constexpr int PRE0 = (VISIT || FUSED0) ? 4 : 0;  // stages before the prolongation
+    static constexpr bool IR0 = POST == POST_IR0;
+    static constexpr int PRE0 = (VISIT || FUSED0 || IR0) ? 4 : 0;  // stages before the prolongation
     static constexpr bool RES = POST != POST_NONE && !VISIT;  // a residual stage follows the relaxation
     static constexpr int LAGR = RES ? 2 * NU + 1 : 0;  // residual stage
     static constexpr int LAST = RES ? LAGR : 2 * NU;   // last stage
     // halo columns: one per stage, two (one lane) for the prolongation slope
     // (VISIT: the slope's two columns lie within the pre-smoothing's four, so
-    // the halo has a column to spare; FUSED0 counts them there too)
-    static constexpr int HX = FUSED0 ? march_halo_x(NU, false, RES) : march_halo_x(NU, PROLONG, RES);
+    // the halo has a column to spare; FUSED0 and IR0 count them there too)
+    static constexpr int HX = (FUSED0 || IR0) ? march_halo_x(NU, false, RES) : march_halo_x(NU, PROLONG, RES);
     static constexpr int HY = (LAST + 1) & ~1;  // halo rows (even: rows start on red parity)
     static constexpr int W = LAST >= 11 ? 18 : (LAST >= 7 ? 14 : 10);  // register window (rows), even
     static constexpr int D = W - LAST - 2;      // prefetch distance (rows)
@@ -142,7 +144,7 @@ struct Cfg {
     // true when the halo has a column to spare beyond the last stage.
     static constexpr bool PAIRST = HX >= 2 * NU + ((PROLONG && !PRE0) ? 2 : 0) + 1;
     static_assert(D >= 1 && DC >= 0, "window too small");
-    static_assert(!VISIT || (NU == 4 && PROLONG), "a visit runs 2 + 2 iterations around the prolongation");
+    static_assert(!(VISIT || IR0) || (NU == 4 && PROLONG), "a visit runs 2 + 2 iterations around the prolongation");
     static_assert(!FUSED0 || (NU == 6 && PROLONG), "FUSED0 runs 2 + 2 + 2 iterations");
 };
 
@@ -150,6 +152,7 @@ struct Cfg {
 struct Tile {
     int n, nm, nc;
     int xo0, x0, xl, I, Il;   // output column start; lane columns; loads; coarse column
+    int xq;                   // POST_IR: loads of the FP64 fields (needed in one column either side of the output)
     bool px, py, wedge, eedge, cwedge, ceedge, outl;
     bool st2;                 // aligned row store of cells x0 - 1, x0 (see march_tile)
     int y0, y1, ys, ye;       // output rows [y0, y1); march rows [ys, ye)
@@ -201,7 +204,15 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
     const T cc = a.cc, invd = a.invd;
 
     const bool subf = a.fmean_part != nullptr;
-    const bool subp = LOADPHI && a.phi_shift != nullptr;
+    // POST_IR: FP64 iterate (Q) and right-hand side (G) rows.  IR: same slots as
+    // P / F.  IR0: the FP64 side only meets the last two stages, so its rows are
+    // loaded DQ rows ahead of those, into a window of half the size.
+    constexpr bool IR0 = C::IR0;
+    constexpr bool IR = POST == POST_IR || IR0;
+    constexpr int WQ = IR ? (IR0 ? W / 2 : W) : 1;
+    constexpr int DQ = 4;
+    static_assert(!IR0 || DQ + 3 <= WQ, "the residual reads three rows of the FP64 iterate");
+    const bool subp = (LOADPHI || IR0) && a.phi_shift != nullptr;
     T fsub = T(0), psub = T(0);
     double psub64 = 0.0;  // POST_IR: the shift applies to the FP64 iterate, in FP64
     if (subf) {
@@ -221,9 +232,6 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
     for (int k = 0; k < W; ++k) P0[k] = P1[k] = F0[k] = F1[k] = T(0);
 #pragma unroll
     for (int k = 0; k < WC; ++k) Cw[k] = T(0);
-    // POST_IR: FP64 iterate (Q) and right-hand side (G) rows, same slots as P / F
-    constexpr bool IR = POST == POST_IR;
-    constexpr int WQ = IR ? W : 1;
     double Q0[WQ], Q1[WQ], G0[WQ], G1[WQ];
 #pragma unroll
     for (int k = 0; k < WQ; ++k) Q0[k] = Q1[k] = G0[k] = G1[k] = 0.0;
@@ -246,15 +254,19 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
             p1 = pr[lo + 1];
         }
     };
+    // The FP64 fields are needed in one row and column around the output only:
+    // the halo's other rows and lanes re-read those (20 B/cell whose halo,
+    // read in full, was 14% more columns and 12 / ty more rows).
+    const int qlo = py ? y0 - 1 : max(y0 - 1, 0), qhi = py ? y1 : min(y1, nm);
     auto load_row64 = [&](int y, double &q0, double &q1, double &g0, double &g1) {
-        y = min(y, ye - 1);
+        y = min(max(y, qlo), qhi);
         const int yy = py ? (y & nm) : y;
         const double *qr = a.q_in + row_off(yy + 1, a.pq_in);
         const double *gr = a.g + row_off(yy + 1, a.pg);
-        q0 = qr[lo];
-        q1 = qr[lo + 1];
-        g0 = gr[lo];
-        g1 = gr[lo + 1];
+        q0 = qr[1 + tl.xq];
+        q1 = qr[2 + tl.xq];
+        g0 = gr[1 + tl.xq];
+        g1 = gr[2 + tl.xq];
     };
     auto load_coarse = [&](int J, T &c) {
         const int Jl = py ? (J & (nc - 1)) : (J < 0 ? 0 : (J >= nc ? nc - 1 : J));
@@ -286,7 +298,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
     static_for<0, D>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         load_row(ys + k, P0[k], P1[k], F0[k], F1[k]);
-        if constexpr (IR) load_row64(ys + k, Q0[k], Q1[k], G0[k], G1[k]);
+        if constexpr (IR && !IR0) load_row64(ys + k, Q0[k], Q1[k], G0[k], G1[k]);
     });
     // Coarse rows sit in a ring: coarse row R in slot (R - ys/2 + 1) mod WC.
     // The prolongation of fine row y reads coarse rows y/2 - 1 .. y/2 + 1; it
@@ -315,7 +327,8 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
             {
                 constexpr int kd = (k + D) % W;
                 load_row(t + D, P0[kd], P1[kd], F0[kd], F1[kd]);
-                if constexpr (IR) load_row64(t + D, Q0[kd], Q1[kd], G0[kd], G1[kd]);
+                constexpr int kq = IR0 ? (k - 2 * NU + DQ + 2 * W) % WQ : kd % WQ;
+                if constexpr (IR) load_row64(IR0 ? t - 2 * NU + DQ : t + D, Q0[kq], Q1[kq], G0[kq], G1[kq]);
             }
             if constexpr (PROLONG) {
                 if constexpr ((k & 1) == 0)
@@ -328,12 +341,13 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
             F0[k] -= fsub;
             F1[k] -= fsub;
             if constexpr (IR) {
+                constexpr int kq = (k - (IR0 ? 2 * NU : 0) + 2 * W) % WQ;
                 if (a.q_zero) {
-                    Q0[k] = 0.0;
-                    Q1[k] = 0.0;
+                    Q0[kq] = 0.0;
+                    Q1[kq] = 0.0;
                 } else if (subp) {
-                    Q0[k] -= psub64;
-                    Q1[k] -= psub64;
+                    Q0[kq] -= psub64;
+                    Q1[kq] -= psub64;
                 }
             }
             if (LOADPHI) {
@@ -541,7 +555,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
                     SB[sv] = p1;
                 }
                 static_for<B + 5, 2 * NU + 1>(stage);
-            } else if constexpr (C::VISIT) {
+            } else if constexpr (C::VISIT || IR0) {
                 // stages 1 .. NU finish the pre-smoothing of row t - NU; its
                 // values are kept (the last pre-smoothing stage of the next
                 // row reads them) before the prolongation adds to them
@@ -559,9 +573,10 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
                 const int y = t - 2 * NU;
                 constexpr int kk = (k - 2 * NU + 2 * W) % W;
                 if constexpr (IR) {
-                    Q0[kk] += (double)P0[kk];
-                    Q1[kk] += (double)P1[kk];
-                    if (inrow(y)) store_row(a.q_out + row_off(y + 1, a.pq_out), Q0[kk], Q1[kk]);
+                    constexpr int kq = kk % WQ;
+                    Q0[kq] += (double)P0[kk];
+                    Q1[kq] += (double)P1[kk];
+                    if (inrow(y)) store_row(a.q_out + row_off(y + 1, a.pq_out), Q0[kq], Q1[kq]);
                 } else if ((FUSED || a.phi_out) && inrow(y)) {  // the fused launch always stores
                     store_row(a.phi_out + row_off(y + 1, a.pout), P0[kk], P1[kk]);
                 }
@@ -570,9 +585,9 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
             if constexpr (IR) {
                 const int y = t - C::LAGR;
                 if (inrow(y)) {
-                    constexpr int kk = (k - C::LAGR + 2 * W) % W;
-                    constexpr int km = (k - C::LAGR - 1 + 2 * W) % W;
-                    constexpr int kp = (k - C::LAGR + 1 + 2 * W) % W;
+                    constexpr int kk = (k - C::LAGR + 2 * W) % WQ;
+                    constexpr int km = (k - C::LAGR - 1 + 2 * W) % WQ;
+                    constexpr int kp = (k - C::LAGR + 1 + 2 * W) % WQ;
                     const double p0 = Q0[kk], p1 = Q1[kk];
                     double w0 = from_left(Q1[kk]);
                     double e1 = from_right(Q0[kk]);
@@ -722,7 +737,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
                 a.partial_norm[2 * tile + 1] = s1;
             }
         }
-    } else if constexpr (POST == POST_NORM || POST == POST_IR || POST == POST_R32) {
+    } else if constexpr (POST == POST_NORM || IR || POST == POST_R32) {
         const double s0 = wave_sum(acc0), s1 = wave_sum(acc1);
         double s2 = 0.0;
         if constexpr (POST != POST_NORM) s2 = wave_sum(acc2);
@@ -781,6 +796,10 @@ __device__ __forceinline__ void march_one(const MarchArgs<T> &a, const int tile)
     tl.x0 = X0 + 2 * lane;
     const bool inx = tl.px || (tl.x0 >= 0 && tl.x0 < tl.n);
     tl.xl = tl.px ? (tl.x0 & tl.nm) : (inx ? tl.x0 : 0);  // out-of-domain lanes read column 0
+    if constexpr (POST == POST_IR || POST == POST_IR0) {
+        const int xc = min(max(tl.x0, tl.xo0 - 2), tl.xo0 + a.outw);
+        tl.xq = tl.px ? (xc & tl.nm) : (xc >= 0 && xc < tl.n ? xc : 0);
+    }
     tl.wedge = !tl.px && tl.x0 == 0;
     tl.eedge = !tl.px && tl.x0 + 1 == tl.nm;
     tl.outl = tl.x0 >= tl.xo0 && tl.x0 < tl.xo0 + a.outw && tl.x0 >= 0 && tl.x0 < tl.n;
