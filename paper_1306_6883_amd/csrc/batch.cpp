@@ -34,7 +34,6 @@ using namespace ccmg;
 namespace {
 
 constexpr int kMaxLevelsB = 16;
-constexpr int kStatBlocksB = 64;
 constexpr int kMinTyB = 8;
 constexpr int kMinOutwB = march_outw(4, false, true);  // the narrowest strips (POST_IR0)
 constexpr int kMaxWaves = 4096;
@@ -59,7 +58,7 @@ struct ProbLay {
     double h = 0;
     size_t lev_a[kMaxLevelsB], lev_b[kMaxLevelsB], lev_f[kMaxLevelsB], fpart[kMaxLevelsB];
     long pitch[kMaxLevelsB];
-    size_t r2 = 0, qb = 0, normpart = 0, part3[2] = {0, 0};
+    size_t r2 = 0, qb = 0, normpart = 0, statpart = 0, part3[2] = {0, 0};
     size_t total = 0;
 };
 
@@ -92,6 +91,7 @@ ProbLay prob_layout(const ccmg_problem &p) {
     pl.r2 = take(sizeof(float) * (size_t)(p.n + 2) * (size_t)pl.pitch[0]);
     pl.qb = take(sizeof(double) * (size_t)(p.n + 2) * (size_t)pl.pitch[0]);
     pl.normpart = take(sizeof(double) * 2 * tiles_max(p.n));
+    pl.statpart = take(sizeof(double) * 4 * tiles_max(p.n));
     pl.part3[0] = take(sizeof(double) * tiles_max(p.n));
     pl.part3[1] = take(sizeof(double) * tiles_max(p.n));
     pl.total = off;
@@ -130,7 +130,7 @@ struct ccmg_batch {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     size_t arena = 0, arena_bytes = 0;
-    size_t off_probs[2] = {0, 0}, off_fin = 0, off_ints = 0, off_hist = 0, off_stat = 0, off_scal = 0;
+    size_t off_probs[2] = {0, 0}, off_fin = 0, off_ints = 0, off_hist = 0, off_scal = 0;
     size_t off_coarse[2] = {0, 0};
     size_t desc_cap = 0, item_cap = 0, off_desc = 0, off_items = 0;
     hipStream_t user = nullptr, stream = nullptr;
@@ -215,6 +215,7 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
         const ProbLay &pl = B->pl[i];
         a.q_in = q_ptr(i, rin);
         a.pq_in = q_pitch(i, rin);
+        a.q_cycles = B->c_guess ? nullptr : B->ints(i) + I_CYC;  // from zero: nothing to read yet
         a.q_out = q_ptr(i, rout);
         a.pq_out = q_pitch(i, rout);
         a.g = B->cf[i];
@@ -338,7 +339,10 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
     }
 }
 
-// The starting pass: r32 = f - A phi (FP64), its norm, and (no guess) phi = 0.
+// The starting pass: r32 = f - A phi (FP64), its norm and f's statistics, from
+// one read of f (a pass of its own for the statistics took 275 us over 512
+// problems).  Without a guess phi is not written: the first step takes it as
+// zero (I_CYC).
 void build_start(const ccmg_batch *B, bool guess, HostLaunch &H) {
     H = HostLaunch();
     H.L.kind = guess ? K_START_GUESS : K_START;
@@ -352,11 +356,10 @@ void build_start(const ccmg_batch *B, bool guess, HostLaunch &H) {
         a.pf = B->cpitch[i];
         a.phi_in = B->cphi[i];
         a.pin = B->cpitch[i];
-        a.phi_out = guess ? nullptr : B->cphi[i];  // writes the zero starting iterate
-        a.pout = B->cpitch[i];
         a.r_out = B->pat<float>(i, pl.lev_f[0]);
         a.pr = pl.pitch[0];
         a.partial = B->pat<double>(i, pl.normpart);
+        a.fstat_part = B->pat<double>(i, pl.statpart);
         a.partial3 = B->pat<double>(i, pl.part3[0]);
         a.count_out = B->ints(i) + I_R32CNT + 0;
         for (int t = 0; t < a.ntiles; ++t) H.items.push_back(WorkItem{(int)H.d64.size(), t});
@@ -415,7 +418,7 @@ std::vector<BatchProb> build_probs(const ccmg_batch *B, int par) {
         b.cycles = B->ints(i) + I_CYC;
         b.normpart = B->pat<double>(i, B->pl[i].normpart);
         b.norm_count = B->ints(i) + I_R32CNT + par;  // written by the launch that wrote normpart
-        b.stat_part = B->at<double>(B->off_stat) + (size_t)4 * kStatBlocksB * i;
+        b.stat_part = B->pat<double>(i, B->pl[i].statpart);
         b.host = B->drec + 8 * i;
     }
     return v;
@@ -493,7 +496,14 @@ hipError_t record_step(ccmg_batch *B, int par) {
         if (e != hipSuccess) return e;
     }
     if (!tail_done) e = launch_coarse_list<float>(B->at<CoarseArgs<float>>(B->off_coarse[par]), B->m, B->stream);
-    if (e == hipSuccess) e = launch_batch_cycle_end(B->at<BatchProb>(B->off_probs[par]), B->m, 0, B->stream);
+    if (e == hipSuccess) e = launch_batch_cycle_end(B->at<BatchProb>(B->off_probs[par]), B->m, B->stream);
+    return e;
+}
+
+// The start of a solve: residual, norm and statistics; every flag and counter set.
+hipError_t record_start(ccmg_batch *B) {
+    hipError_t e = launch_one(B, B->start);
+    if (e == hipSuccess) e = launch_batch_start(B->at<BatchProb>(B->off_probs[0]), B->m, B->stream);
     return e;
 }
 
@@ -583,7 +593,7 @@ size_t ccmg_batch_workspace_bytes(int m, const ccmg_problem *probs) {
     // arena: 2 parities x (pre + post launches) + the start pass
     const size_t per = al256(sizeof(BatchProb) * m) * 2 + al256(sizeof(BatchFinish) * m) +
                        al256(sizeof(int) * kInts * m) + al256(sizeof(double) * CCMG_HISTORY * m) +
-                       al256(sizeof(double) * 4 * kStatBlocksB * m) + al256(sizeof(double) * kScal * m) +
+                       al256(sizeof(double) * kScal * m) +
                        al256(sizeof(CoarseArgs<float>) * m) * 2;
     const size_t dcap = al256((descs * 2 * 2 + 2 * m) * sizeof(MarchArgs<double>) + 64 * 256);
     const size_t icap = al256((items * 2 * 2 + items) * sizeof(WorkItem) + 64 * 256);
@@ -627,7 +637,6 @@ int ccmg_batch_create(int m, const ccmg_problem *probs, void *d_ws, size_t ws_by
     B->off_fin = take(sizeof(BatchFinish) * m);
     B->off_ints = take(sizeof(int) * kInts * m);
     B->off_hist = take(sizeof(double) * CCMG_HISTORY * m);
-    B->off_stat = take(sizeof(double) * 4 * kStatBlocksB * m);
     B->off_scal = take(sizeof(double) * kScal * m);
     B->off_coarse[0] = take(sizeof(CoarseArgs<float>) * m);
     B->off_coarse[1] = take(sizeof(CoarseArgs<float>) * m);
@@ -706,10 +715,8 @@ int ccmg_batch_solve(ccmg_batch *B, const double *const *d_f, double *const *d_p
     if (e == hipSuccess) e = prepare(B, d_f, d_phi, pitch, use_guess != 0, false);
     if (e != hipSuccess) return CCMG_EHIP;
     e = hipEventRecord(B->ev_t0, B->stream);
-    // statistics, flags, the starting FP64 residual and its norm
-    if (e == hipSuccess) e = launch_batch_fstats(B->at<BatchProb>(B->off_probs[0]), m, kStatBlocksB, B->stream);
-    if (e == hipSuccess) e = launch_one(B, B->start);
-    if (e == hipSuccess) e = launch_batch_cycle_end(B->at<BatchProb>(B->off_probs[0]), m, 1, B->stream);
+    // flags, the starting FP64 residual and its norm, statistics
+    if (e == hipSuccess) e = record_start(B);
     if (e == hipSuccess) e = hipStreamSynchronize(B->stream);
     if (e != hipSuccess) return CCMG_EHIP;
     int max_steps = 0;
@@ -766,7 +773,8 @@ int ccmg_batch_solve(ccmg_batch *B, const double *const *d_f, double *const *d_p
         q.n = B->prob[i].n;
         for (int s = 0; s < 4; ++s) q.bc[s] = B->prob[i].bc[s];
         q.shift = singular_of(B->prob[i]) ? B->at<double>(B->off_scal) + (size_t)kScal * i + S_PHIMEAN : nullptr;
-        q.zero = scal[(size_t)kScal * i + S_F2] == 0.0 ? 1 : 0;
+        // (done before its first step, from zero: nothing has written the iterate)
+        q.zero = scal[(size_t)kScal * i + S_F2] == 0.0 || (c == 0 && !use_guess) ? 1 : 0;
         nmax = std::max(nmax, q.n);
     }
     e = hipMemcpyAsync(B->ws + B->off_fin, fin.data(), sizeof(BatchFinish) * m, hipMemcpyHostToDevice, B->stream);
@@ -831,9 +839,7 @@ int ccmg_batch_autotune(ccmg_batch *B, const double *const *d_f, double *const *
     const int cands[] = {8, 16, 32, 64, 128};
     const int wave_cands[] = {1024, 2048, 4096, 8192, 32768};
     auto time_steps = [&](float &ms) -> hipError_t {
-        hipError_t x = launch_batch_fstats(B->at<BatchProb>(B->off_probs[0]), B->m, kStatBlocksB, B->stream);
-        if (x == hipSuccess) x = launch_one(B, B->start);
-        if (x == hipSuccess) x = launch_batch_cycle_end(B->at<BatchProb>(B->off_probs[0]), B->m, 1, B->stream);
+        hipError_t x = record_start(B);
         if (x == hipSuccess) x = hipEventRecord(e0, B->stream);
         for (int k = 1; k <= 2 && x == hipSuccess; ++k) x = hipGraphLaunch(B->graph[k & 1], B->stream);
         if (x == hipSuccess) x = hipEventRecord(e1, B->stream);

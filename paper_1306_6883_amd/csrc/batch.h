@@ -18,7 +18,7 @@ struct BatchProb {
     int *cycles;          // steps performed
     const double *normpart;  // per-tile (sum r^2, sum phi) of the last FP64 residual pass
     const int *norm_count;   // how many tiles wrote them
-    double *stat_part;    // per-block statistics of f
+    const double *stat_part;  // per-tile statistics of f
     double *host;         // host-mapped [rho, cycles, done]
 };
 
@@ -31,11 +31,11 @@ struct BatchFinish {
     int n;
     int bc[4];
     const double *shift;  // mean removed from singular problems (or null)
-    int zero;             // f == 0: the returned field is 0 (valid and ghost cells)
+    int zero;             // the returned field is 0 (valid and ghost cells)
 };
 
-hipError_t launch_batch_fstats(const BatchProb *probs, int m, int blocks, hipStream_t s);
-hipError_t launch_batch_cycle_end(const BatchProb *probs, int m, int start, hipStream_t s);
+hipError_t launch_batch_start(const BatchProb *probs, int m, hipStream_t s);
+hipError_t launch_batch_cycle_end(const BatchProb *probs, int m, hipStream_t s);
 hipError_t launch_batch_finish(const BatchFinish *fin, int m, int nmax, hipStream_t s);
 
 }  // namespace ccmg

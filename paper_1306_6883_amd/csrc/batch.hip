@@ -22,61 +22,10 @@ __device__ double block_sum256(double v, double *red) {
 __device__ __forceinline__ double side_sign(int b) { return b == CCMG_BC_DIRICHLET ? -1.0 : 1.0; }
 }  // namespace
 
-// grid (kStatBlocksPerProblem, m): partial statistics of f for each problem.
-__global__ __launch_bounds__(kRed) void k_batch_fstats(const BatchProb *__restrict__ probs) {
-    __shared__ double red[4];
-    const BatchProb &p = probs[blockIdx.y];
-    double s = 0.0, sa = 0.0, s2 = 0.0, bad = 0.0;
-    for (int y = blockIdx.x; y < p.n; y += gridDim.x) {
-        const double *row = p.f + (long)(y + 1) * p.pf + 1;
-        for (int x = threadIdx.x; x < p.n; x += kRed) {
-            const double v = row[x];
-            if (!isfinite(v)) {
-                bad += 1.0;
-                continue;
-            }
-            s += v;
-            sa += fabs(v);
-            s2 += v * v;
-        }
-    }
-    s = block_sum256(s, red);
-    sa = block_sum256(sa, red);
-    s2 = block_sum256(s2, red);
-    bad = block_sum256(bad, red);
-    if (threadIdx.x == 0) {
-        double *o = p.stat_part + 4 * blockIdx.x;
-        o[0] = s;
-        o[1] = sa;
-        o[2] = s2;
-        o[3] = bad;
-    }
-}
-
-// one workgroup per problem: totals of the statistics, flags and counters reset.
-__global__ __launch_bounds__(kRed) void k_batch_fstats_reduce(const BatchProb *__restrict__ probs, int blocks) {
-    __shared__ double red[4];
-    const BatchProb &p = probs[blockIdx.x];
-    double t[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = threadIdx.x; i < blocks; i += kRed)
-        for (int q = 0; q < 4; ++q) t[q] += p.stat_part[4 * i + q];
-    for (int q = 0; q < 4; ++q) t[q] = block_sum256(t[q], red);
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < 4; ++q) p.scal[q] = t[q];  // sum f, sum |f|, sum f^2, non-finite count
-        p.scal[S_PHIMEAN] = 0.0;
-        *p.done = 0;
-        *p.cycles = 0;
-        p.host[2] = 0.0;
-    }
-}
-
-// End of a batched step (or of the starting residual pass when `start`): per
-// problem, the relative residual of the FP64 iterate and the mean of phi from
-// the per-tile partial sums, the history, the cycle count and the done flag.
-__global__ __launch_bounds__(kRed) void k_batch_cycle_end(const BatchProb *__restrict__ probs, int start) {
-    __shared__ double red[4];
-    const BatchProb &p = probs[blockIdx.x];
-    if (*p.done) return;  // uniform over the workgroup
+// One workgroup per problem: the relative residual of the FP64 iterate and the
+// mean of phi from the per-tile partial sums, the history, the cycle count and
+// the done flag.
+__device__ void file_cycle(const BatchProb &p, double f2, int c, double *red) {
     const int count = *p.norm_count;
     double s0 = 0.0, s1 = 0.0;
     for (int i = threadIdx.x; i < count; i += kRed) {
@@ -86,13 +35,12 @@ __global__ __launch_bounds__(kRed) void k_batch_cycle_end(const BatchProb *__res
     s0 = block_sum256(s0, red);
     s1 = block_sum256(s1, red);
     if (threadIdx.x == 0) {
-        const double rho = sqrt(s0) / sqrt(p.scal[S_F2]);
-        const int c = start ? 0 : *p.cycles + 1;
+        const double rho = sqrt(s0) / sqrt(f2);
         *p.cycles = c;
         if (c < CCMG_HISTORY) p.hist[c] = rho;
         p.scal[S_PHIMEAN] = p.singular ? s1 / ((double)p.n * (double)p.n) : 0.0;
         const bool fin = rho <= p.rtol || !isfinite(rho) || c >= p.max_cycles;
-        if (fin) *p.done = 1;
+        *p.done = fin ? 1 : 0;
         // host-mapped summary: rho, cycles, done
         p.host[0] = rho;
         p.host[1] = (double)c;
@@ -100,12 +48,37 @@ __global__ __launch_bounds__(kRed) void k_batch_cycle_end(const BatchProb *__res
     }
 }
 
+// End of the starting pass: the totals of f's statistics over the same tiles
+// (sum f, sum |f|, sum f^2, non-finite count), then as after a step.
+__global__ __launch_bounds__(kRed) void k_batch_start(const BatchProb *__restrict__ probs) {
+    __shared__ double red[4];
+    const BatchProb &p = probs[blockIdx.x];
+    const int count = *p.norm_count;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < count; i += kRed)
+        for (int q = 0; q < 4; ++q) t[q] += p.stat_part[4 * i + q];
+    for (int q = 0; q < 4; ++q) t[q] = block_sum256(t[q], red);
+    if (threadIdx.x == 0)
+        for (int q = 0; q < 4; ++q) p.scal[q] = t[q];
+    file_cycle(p, t[2], 0, red);
+}
+
+// End of a batched step.
+__global__ __launch_bounds__(kRed) void k_batch_cycle_end(const BatchProb *__restrict__ probs) {
+    __shared__ double red[4];
+    const BatchProb &p = probs[blockIdx.x];
+    if (*p.done) return;  // uniform over the workgroup
+    const int c = *p.cycles + 1;
+    file_cycle(p, p.scal[S_F2], c, red);
+}
+
 // grid (rows, m): the returned field.  Valid cells: copy from where the last
 // step left the iterate (if that is not the caller's array) and remove the
-// mean of singular problems; zeros for a zero right-hand side (whatever the
+// mean of singular problems (nothing to do where neither applies); zeros for a zero right-hand side (whatever the
 // guess was), as a single solve returns.
 __global__ __launch_bounds__(kRed) void k_batch_finish_valid(const BatchFinish *__restrict__ fin) {
     const BatchFinish &q = fin[blockIdx.y];
+    if (!q.zero && !q.shift && q.src == q.dst) return;
     const double m = q.shift ? *q.shift : 0.0;
     for (int y = blockIdx.x; y < q.n; y += gridDim.x) {
         const double *src = q.src + (long)(y + 1) * q.psrc + 1;
@@ -135,14 +108,13 @@ __global__ __launch_bounds__(kRed) void k_batch_finish_ghosts(const BatchFinish 
     a[(long)(n + 1) * pitch + 1 + k] = q.bc[3] == CCMG_BC_PERIODIC ? clo : side_sign(q.bc[3]) * chi;
 }
 
-hipError_t launch_batch_fstats(const BatchProb *probs, int m, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_fstats, dim3(blocks, m), dim3(kRed), 0, s, probs);
-    hipLaunchKernelGGL(k_batch_fstats_reduce, dim3(m), dim3(kRed), 0, s, probs, blocks);
+hipError_t launch_batch_start(const BatchProb *probs, int m, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_start, dim3(m), dim3(kRed), 0, s, probs);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_cycle_end(const BatchProb *probs, int m, int start, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_cycle_end, dim3(m), dim3(kRed), 0, s, probs, start);
+hipError_t launch_batch_cycle_end(const BatchProb *probs, int m, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_cycle_end, dim3(m), dim3(kRed), 0, s, probs);
     return hipGetLastError();
 }
 

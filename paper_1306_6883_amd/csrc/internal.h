@@ -94,6 +94,7 @@ struct MarchArgs {
     double *partial3;    // per tile: sum of the FP32 residual (mean removal of singular problems)
     double alpha64, beta64, ih2_64;
     int q_zero;          // POST_IR: the FP64 iterate is zero (q_in is not used)
+    const int *q_cycles; // ... or it is if this device counter (if set) is 0
     int *count_out;      // if set, receives ntiles (producers of per-tile sums)
     // POST_FUSED: the iterate after the post-smoothing and its per-tile norm sums
     T *phi_mid;

@@ -257,11 +257,15 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
     // The FP64 fields are needed in one row and column around the output only:
     // the halo's other rows and lanes re-read those (20 B/cell whose halo,
     // read in full, was 14% more columns and 12 / ty more rows).
+    // An iterate that is zero isn't read: its loads repeat the right-hand side's.
+    const bool qz = IR && (a.q_zero || (a.q_cycles && *a.q_cycles == 0));
+    const double *const qsrc = qz ? a.g : a.q_in;
+    const int pqs = qz ? a.pg : a.pq_in;
     const int qlo = py ? y0 - 1 : max(y0 - 1, 0), qhi = py ? y1 : min(y1, nm);
     auto load_row64 = [&](int y, double &q0, double &q1, double &g0, double &g1) {
         y = min(max(y, qlo), qhi);
         const int yy = py ? (y & nm) : y;
-        const double *qr = a.q_in + row_off(yy + 1, a.pq_in);
+        const double *qr = qsrc + row_off(yy + 1, pqs);
         const double *gr = a.g + row_off(yy + 1, a.pg);
         q0 = qr[1 + tl.xq];
         q1 = qr[2 + tl.xq];
@@ -342,7 +346,7 @@ __device__ __forceinline__ void march_tile(const MarchArgs<T> &a, const Tile &tl
             F1[k] -= fsub;
             if constexpr (IR) {
                 constexpr int kq = (k - (IR0 ? 2 * NU : 0) + 2 * W) % WQ;
-                if (a.q_zero) {
+                if (qz) {
                     Q0[kq] = 0.0;
                     Q1[kq] = 0.0;
                 } else if (subp) {

@@ -57,3 +57,22 @@ def test_recomputed_levels_with_a_guess_and_a_mean():
     res = f[1:n + 1, 1:n + 1] - lap * float(n * n)
     assert res.norm().item() / f[1:n + 1, 1:n + 1].norm().item() <= 1.5e-9
     assert abs(u.mean().item()) <= 1e-12 * u.abs().max().item()
+
+
+def test_problems_done_before_their_first_step_return_zero():
+    """From zero, whatever the array held: a zero right-hand side, a tolerance
+    that zero meets, and a right-hand side that isn't finite; a problem beside
+    them that takes steps is solved."""
+    n = 64
+    fs = [field(n, 0), field(n, 1, seed=1), field(n, 0, seed=2), field(n, 1, seed=3)]
+    fs[2][5, 7] = float("nan")
+    phis = [field(n, i % 2, seed=20 + i) for i in range(4)]
+    probs = [cc.Problem(n=n, bc=tuple("DDDD"), rtol=r, prec=cc.MIXED) for r in (1e-9, 2.0, 1e-9, 1e-9)]
+    res, _ = cc.ccmg_batch_solve(cc.Batch(probs), fs, phis)
+    assert [r.status for r in res] == [cc.OK, cc.OK, cc.ENONFINITE, cc.OK]
+    assert [r.cycles for r in res[:3]] == [0, 0, 0] and res[3].cycles > 0
+    for p in phis[:3]:
+        # (the four corner ghosts are nobody's)
+        assert torch.count_nonzero(p[1:n + 1, :n + 2]).item() == 0
+        assert torch.count_nonzero(p[:, 1:n + 1]).item() == 0
+    assert phis[3][1:n + 1, 1:n + 1].abs().max().item() > 0
