@@ -41,15 +41,20 @@ constexpr int kMaxWaves = 4096;
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 long pitch_of(int n) { return (long)((n + 2 + 31) & ~31); }
 int tiles_max(int n) { return ((n + kMinOutwB - 1) / kMinOutwB) * ((n + kMinTyB - 1) / kMinTyB); }
-// Levels of this many cells per side on recompute the iterate the way down left
-// instead of storing and reading it back (8 of the 46 or 22 B/cell): the finest
-// level's last launch from 256 on, a coarser level's visit from 512 on.  In a
-// step of 512 problems: 1024^2 907 -> 807 us and 225 -> 153 for its way down;
-// 512^2 238 -> 206 and 137 -> 97, coarser 512^2 95 -> 69 and 97 -> 74; 256^2
-// 69 -> 62 and 62 -> 51.  Below, the fields come from the caches and the 8 more
-// halo rows cost what they save (128^2 33 -> 36 and 28 -> 26, 64^2 19 -> 27).
+// Size classes whose levels recompute the iterate the way down left instead of
+// storing and reading it back (8 of the 46 or 22 B/cell): the finest levels'
+// last launch from 256^2 on, a coarser level's visit from 512^2 on.  In a step
+// of 512 problems: 1024^2 907 -> 807 us and 225 -> 153 for its way down; 512^2
+// 238 -> 206 and 137 -> 97, coarser 512^2 95 -> 69 and 97 -> 74; 256^2 69 -> 62
+// and 62 -> 51.  Below, the 8 more halo rows cost what they save (128^2 33 -> 36
+// and 28 -> 26, 64^2 19 -> 27).  And only where the class's cells don't fit the
+// caches anyway (4 M cells of finest levels, 8 M of coarser): batches of 16, 32,
+// 64, 128 and 256 problems take 2869, 3183, 4776, 7519 and 13714 us so, with
+// half the two lines 2864, 3335, 4747, 7519 and 13711, with twice 2863, 3189,
+// 4771, 7519 and 13846, and without recomputation 2867, 3189, 4763, 7694 and
+// 14434.
 constexpr int kRecomputeFinest = 256, kRecomputeCoarse = 512;
-bool recomputes(int n, int l) { return (n >> l) >= (l == 0 ? kRecomputeFinest : kRecomputeCoarse); }
+constexpr double kRecomputeFinestCells = 4.0 * 1048576.0, kRecomputeCoarseCells = 8.0 * 1048576.0;
 int log2i(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 // Per-problem workspace (FP32 levels, FP64 second iterate, partial sums).
@@ -139,6 +144,8 @@ struct ccmg_batch {
     double *hrec = nullptr, *drec = nullptr;   // host-mapped per-problem records
     std::map<int, int> ty;                     // rows per band for each level size class
     std::vector<int> sizes;                    // march level sizes present (descending)
+    std::map<int, bool> rec_finest, rec_coarse;  // size classes whose levels recompute (finest; coarser)
+    bool recomputes(int n, int l) const { return (l == 0 ? rec_finest : rec_coarse).at(n >> l); }
     int waves = kMaxWaves;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     bool graph_ok = false;
@@ -260,7 +267,7 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
             fmean_fill(i, l, a);
             a.phi_in = B->pat<float>(i, pl.lev_a[l]);
             a.pin = pl.pitch[l];
-            a.phi_out = recomputes(p.n, l) ? nullptr : B->pat<float>(i, pl.lev_b[l]);
+            a.phi_out = B->recomputes(p.n, l) ? nullptr : B->pat<float>(i, pl.lev_b[l]);
             a.pout = pl.pitch[l];
             a.aux = B->pat<float>(i, pl.lev_f[l + 1]);
             a.paux = pl.pitch[l + 1];
@@ -277,9 +284,8 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
     std::vector<int> asc(B->sizes.rbegin(), B->sizes.rend());
     for (int s : asc) {
         HostLaunch HC, HF;
-        // (a size class is one side of the line for all its problems)
-        HC.L.kind = s >= kRecomputeCoarse ? K_VISIT : K_POSTC;
-        HF.L.kind = s >= kRecomputeFinest ? K_POSTF0 : K_POSTF;
+        HC.L.kind = B->rec_coarse.at(s) ? K_VISIT : K_POSTC;
+        HF.L.kind = B->rec_finest.at(s) ? K_POSTF0 : K_POSTF;
         HC.L.size = HF.L.size = s;
         for (int i = 0; i < B->m; ++i) {
             const ccmg_problem &p = B->prob[i];
@@ -289,7 +295,7 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
             if (l >= pl.lt) continue;
             MarchArgs<float> a{};
             consts_for(p, pl, l, a);
-            const bool rec = recomputes(p.n, l);
+            const bool rec = B->recomputes(p.n, l);
             set_tiles(a, l == 0 ? (rec ? march_outw(4, false, true) : march_outw(2, true, true))
                                 : (rec ? march_outw(4, true, false) : march_outw(2, true, false)),
                       B->ty.at(s));
@@ -651,6 +657,10 @@ int ccmg_batch_create(int m, const ccmg_problem *probs, void *d_ws, size_t ws_by
         const int s = kv.first;
         kv.second = s >= 512 ? 16 : 8;
         B->sizes.push_back(s);
+        double finest = 0.0, coarse = 0.0;
+        for (int i = 0; i < m; ++i) (probs[i].n == s ? finest : coarse) += probs[i].n >= s ? (double)s * s : 0.0;
+        B->rec_finest[s] = s >= kRecomputeFinest && finest >= kRecomputeFinestCells;
+        B->rec_coarse[s] = s >= kRecomputeCoarse && coarse >= kRecomputeCoarseCells;
     }
     std::sort(B->sizes.rbegin(), B->sizes.rend());
     B->user = static_cast<hipStream_t>(stream);

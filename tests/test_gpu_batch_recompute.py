@@ -41,6 +41,31 @@ def test_recomputed_levels_match_single_solves(tuned):
         assert torch.equal(phi[1:n + 1, 1:n + 1], one[1:n + 1, 1:n + 1]), (n, bc)
 
 
+@pytest.mark.parametrize("counts", [{256: 63}, {256: 64, 512: 16}, {1024: 33}, {1024: 24, 2048: 8}])
+def test_size_classes_on_either_side_of_the_cell_counts(counts):
+    """Batches whose size classes hold just fewer or just enough cells to
+    recompute (4 M of finest levels, 8 M of a coarser level): two of each size
+    against the same problems alone."""
+    cases = [(n, ("DDDD", "NDPP")[i % 2]) for n, c in counts.items() for i in range(c)]
+    probs = [cc.Problem(n=n, bc=tuple(bc), rtol=1e-9, prec=cc.MIXED) for n, bc in cases]
+    fs = [field(n, 0, seed=i) for i, (n, _) in enumerate(cases)]
+    phis = [field(n, 0) for n, _ in cases]
+    res, info = cc.ccmg_batch_solve(cc.Batch(probs), fs, phis)
+    assert info["status"] == cc.OK
+    seen = {}
+    for (n, bc), p, f, phi, r in zip(cases, probs, fs, phis, res):
+        seen[n, bc] = seen.get((n, bc), 0) + 1
+        if seen[n, bc] > 1:
+            continue
+        plan = cc.Plan(p)
+        cc.ccmg_plan_set_option(plan, cc.OPT_MIXED_INNER, 1)
+        one = torch.zeros_like(f)
+        r1 = cc.ccmg_solve(plan, f, one)
+        assert r1.cycles == r.cycles, (n, bc)
+        np.testing.assert_allclose(r.history, r1.history, rtol=n * n * 2.0 ** -52)
+        assert torch.equal(phi[1:n + 1, 1:n + 1], one[1:n + 1, 1:n + 1]), (n, bc)
+
+
 def test_recomputed_levels_with_a_guess_and_a_mean():
     """A singular problem (its mean is removed as the iterate is read) from a
     guess: the residual of what is returned is the one reported."""
