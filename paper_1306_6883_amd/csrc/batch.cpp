@@ -6,8 +6,9 @@
 // batch is a fixed sequence of launches:
 //   for each level size s, largest first: one persistent row-march launch over
 //     the (problem, tile) list of every problem that has a level of size s
-//     (relaxation + residual + restriction);
-//   one launch with one workgroup per problem for the levels of <= 32 cells;
+//     (relaxation + residual + restriction; the iterate is stored only where
+//     the way up does not recompute it);
+//   one launch with one wavefront per problem for the levels of <= 32 cells;
 //   for each size s, smallest first: the prolongating launches (coarse levels,
 //     and the finest levels with the FP64 update);
 //   one launch that turns each problem's partial sums into its relative
@@ -279,7 +280,7 @@ void build_step(const ccmg_batch *B, int par, std::vector<HostLaunch> &out) {
         }
         if (!H.d32.empty()) out.push_back(std::move(H));
     }
-    // (the one-workgroup tail is launched between the two halves; see record_step)
+    // (the tail is launched between the two halves; see record_step)
     // up: prolongation + relaxation, coarse levels and finest levels apart
     std::vector<int> asc(B->sizes.rbegin(), B->sizes.rend());
     for (int s : asc) {

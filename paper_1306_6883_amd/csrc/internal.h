@@ -180,7 +180,7 @@ hipError_t dispatch_nu(const MarchArgs<T> &a, bool load_phi, bool prolong, int p
                        hipStream_t s, int *nt);
 
 // Coarse tail: a whole V-cycle from level `n_top` (<= kCoarseMax) down to 2x2 and
-// back, one workgroup, all levels resident in LDS (coarse.hip).
+// back, one wavefront (smaller finest grids: one workgroup on LDS; coarse.hip).
 constexpr int kCoarseMax = 32;
 template <typename T>
 struct CoarseArgs {
