@@ -50,12 +50,25 @@ int tiles_max(int n) { return ((n + kMinOutwB - 1) / kMinOutwB) * ((n + kMinTyB 
 // and 62 -> 51.  Below, the 8 more halo rows cost what they save (128^2 33 -> 36
 // and 28 -> 26, 64^2 19 -> 27).  And only where the class's cells don't fit the
 // caches anyway (4 M cells of finest levels, 8 M of coarser): batches of 16, 32,
-// 64, 128 and 256 problems take 2869, 3183, 4776, 7519 and 13714 us so, with
+// 64, 128 and 256 problems (in bands of 8 and 16 rows) took 2869, 3183, 4776, 7519 and 13714 us so, with
 // half the two lines 2864, 3335, 4747, 7519 and 13711, with twice 2863, 3189,
 // 4771, 7519 and 13846, and without recomputation 2867, 3189, 4763, 7694 and
 // 14434.
 constexpr int kRecomputeFinest = 256, kRecomputeCoarse = 512;
 constexpr double kRecomputeFinestCells = 4.0 * 1048576.0, kRecomputeCoarseCells = 8.0 * 1048576.0;
+// Rows per band before autotuning, for `levels` levels of s cells per side: as
+// tall as leaves two waves per SIMD of the 1024 (the halo is 12 - 20 rows a
+// band, whatever its height), at least 16 rows from 512^2 and 8 below, where
+// small batches need the waves.  Untuned batches of 64, 96, 128, 192, 256 and
+// 512 problems take 4745, 6738, 7087, 10037, 11845 and 22080 us so, with those
+// least heights everywhere 4797, 7289, 7529, 11379, 13709 and 26380; what the
+// tuner finds beyond it is 1 - 2%.
+int default_rows(int s, long levels) {
+    int ty = s >= 512 ? 16 : 8;
+    const long strips = (s + kMinOutwB - 1) / kMinOutwB;
+    while (2 * ty <= std::min(128, s / 4) && levels * strips * (s / (2 * ty)) >= 2048) ty *= 2;
+    return ty;
+}
 int log2i(int n) { return 31 - __builtin_clz((unsigned)n); }
 
 // Per-problem workspace (FP32 levels, FP64 second iterate, partial sums).
@@ -656,10 +669,15 @@ int ccmg_batch_create(int m, const ccmg_problem *probs, void *d_ws, size_t ws_by
         for (int l = 0; l < B->pl[i].lt; ++l) B->ty[probs[i].n >> l] = 0;
     for (auto &kv : B->ty) {
         const int s = kv.first;
-        kv.second = s >= 512 ? 16 : 8;
         B->sizes.push_back(s);
         double finest = 0.0, coarse = 0.0;
-        for (int i = 0; i < m; ++i) (probs[i].n == s ? finest : coarse) += probs[i].n >= s ? (double)s * s : 0.0;
+        long levels = 0;
+        for (int i = 0; i < m; ++i) {
+            if (probs[i].n < s) continue;
+            (probs[i].n == s ? finest : coarse) += (double)s * s;
+            ++levels;
+        }
+        kv.second = default_rows(s, levels);
         B->rec_finest[s] = s >= kRecomputeFinest && finest >= kRecomputeFinestCells;
         B->rec_coarse[s] = s >= kRecomputeCoarse && coarse >= kRecomputeCoarseCells;
     }
