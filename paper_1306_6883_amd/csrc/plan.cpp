@@ -2100,7 +2100,9 @@ hipError_t enqueue_fused_cycle(ccmg_plan *P, FusedCtx &cx, const double *d_f, lo
         cx.next = Buf<double>{nullptr, 0};
         cx.cur = A;
     }
-    if (P->pend_may) {
+    // only a fused end: after a plain one the next cycle starts on the finest
+    // level, in a launch that needs the done flag and the mean of phi
+    if (end_fused && P->pend_may) {
         P->pend = cycle_end_args(P, nt, slot, P->singular, true, true);
         P->pend_on = true;
         return hipSuccess;
