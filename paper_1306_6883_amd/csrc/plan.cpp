@@ -2358,7 +2358,12 @@ int ccmg::solve_impl(ccmg_plan *P, const double *d_f, double *d_phi, ptrdiff_t p
     // cycle's first coarse launch where that is one of bands held in registers.
     // From 256^2: the host reads the residual a launch later, and below that
     // what is left of the cycle is shorter than queueing the next one.
-    P->pend_on = false;
+    // However the solve ends, no end of a cycle queued past the last is left
+    // for another call's coarse launches.
+    struct NoEndLeft {
+        ccmg_plan *plan;
+        ~NoEndLeft() { plan->pend_on = plan->pend_may = false; }
+    } no_end_left{P};
     P->pend_may = fused && n >= 256 &&
                   block_runs(n / 2, 2, false, false, POST_RESTRICT, visit_level(P, 1) ? P->shp_pre_v[1] : P->shp_pre[1],
                              true);

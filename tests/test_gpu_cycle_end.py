@@ -59,3 +59,38 @@ def test_cycle_queued_past_the_last_one_does_nothing(bc):
     assert r.status == s.status == cc.OK and r.cycles == s.cycles == 4
     assert np.array_equal(phi, ref)
     assert torch.equal(buf, ref_buf)
+
+
+def history_region(plan):
+    """The device history of a plan: behind it lie the flags (256 bytes) and
+    the exact bottom's inverse (8^4 doubles), the workspace's end."""
+    ws, nbytes = workspace(plan), cc.ccmg_workspace_bytes(plan.prob)
+    end = nbytes - 8 * 8 ** 4 - 256
+    return ws[end - 8 * cc.HISTORY:end].clone().view(torch.float64)
+
+
+@pytest.mark.parametrize("value", [0.0, np.inf])
+def test_refused_solve_leaves_no_end_behind(value):
+    """A right-hand side that ends a solve is seen after its first cycle, when
+    the second is queued and its end not yet launched; that end must not be run
+    by whatever uses the plan next (here the autotuner's coarse cycles, which
+    write no history: it is cleared and stays clear)."""
+    n = 4096
+    plan = cc.Plan(cc.Problem(n=n, bc=tuple("DDDD")))
+    good = np.random.default_rng(3).standard_normal((n, n))
+    bad = field(np.full((n, n), value))
+    phi = torch.zeros_like(bad)
+    if value == 0.0:
+        r = cc.ccmg_solve(plan, bad, phi)
+        assert r.status == cc.OK and r.cycles == 0
+    else:
+        with pytest.raises(cc.CcmgError) as e:
+            cc.ccmg_solve(plan, bad, phi)
+        assert e.value.status == cc.ENONFINITE
+    f = field(good)
+    phi.zero_()
+    cc.ccmg_plan_autotune(plan, f, phi)
+    torch.cuda.synchronize()
+    assert not history_region(plan).any()
+    r = cc.ccmg_solve(plan, f, phi)
+    assert r.status == cc.OK and r.cycles > 5
