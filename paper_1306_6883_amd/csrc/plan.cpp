@@ -173,8 +173,16 @@ MarchShape shape_for(int n) {
 // 112 against 114 - 120).  Four waves per workgroup where singular plans would
 // else write over a thousand partial sums (fused, 2048^2 periodic: 110.6
 // against 115.6 us), one elsewhere (2048^2 Dirichlet: 112.1 against 114.3).
-MarchShape level_shape_for(int n, bool singular) {
+// A launch that has no such variant (`held` false: POST_IR, or a smoothing
+// count other than two) marches the rows: 8 to 512^2 (V(1,1) there 1189 us
+// against 1257 with 16), 16 at 1024^2, and 32 at 2048^2, where 16 carry ten
+// halo rows: untuned mixed solves 1055 and, periodic, 1214 us with 16, 1019 and
+// 1149 with 32; V(1,1) 2686 and 2445 against 2646 and 2377.
+// (The first launch of a Crank-Nicolson step and of a full multigrid start
+// has none either, but runs once a solve: from 8 to 64 rows within 1%.)
+MarchShape level_shape_for(int n, bool singular, bool held) {
     if (n < 64 || n > 2048) return shape_for(n);
+    if (!held) return n >= 1024 ? shape_for(n) : MarchShape{8, 1};
     return n >= 1024 ? MarchShape{16, singular ? 4 : 1} : MarchShape{8, 1};
 }
 MarchShape fused_shape_for(int n, bool f64, bool singular) {
@@ -1037,7 +1045,12 @@ void plan_init_host(ccmg_plan *P, const ccmg_problem &p) {
     P->singular = p.alpha == 0.0 && p.bc[0] != CCMG_BC_DIRICHLET && p.bc[1] != CCMG_BC_DIRICHLET &&
                   p.bc[2] != CCMG_BC_DIRICHLET && p.bc[3] != CCMG_BC_DIRICHLET;
     for (int l = 0; l < P->lay.L && l < kMaxLevels; ++l) {
-        P->shp_pre[l] = P->shp_post[l] = P->shp_pre_v[l] = level_shape_for(P->lay.lev[l].n, P->singular);
+        // (held in registers: the restricting launch ends with two iterations,
+        // the prolongating one begins with two and does not update FP64 fields)
+        const int n = P->lay.lev[l].n;
+        const bool post_held = p.nu2 >= 2 && p.nu2 % 2 == 0 && !(l == 0 && p.prec == CCMG_MIXED);
+        P->shp_pre[l] = P->shp_pre_v[l] = level_shape_for(n, P->singular, p.nu1 >= 2);
+        P->shp_post[l] = level_shape_for(n, P->singular, post_held);
         P->shp_visit[l] = visit_shape_for(P->lay.lev[l].n);
         P->visit[l] = false;
     }
