@@ -110,8 +110,9 @@ hipError_t forward(ccmg_net *N, const float *x, float *y, int nb) {
             hipLaunchKernelGGL(k_conv32<true>, dim3(nb * kNetG / seg), dim3(256), 0, s, N->act(l - 1), N->act_lo(l - 1),
                                wl, wlo, N->act(l), N->act_lo(l), dil, seg);
     }
-    hipLaunchKernelGGL(k_conv_out, dim3(nb * net_dilation(5)), dim3(256), 0, s, N->act(4), N->act_lo(4),
-                       N->w() + net_param_offset(5), y);
+    const int outs = nb <= kConvOutSplitMaxBatch ? 1 : 2;
+    hipLaunchKernelGGL(outs == 1 ? k_conv_out<1> : k_conv_out<2>, dim3(nb * net_dilation(5) * 2 / outs), dim3(256), 0, s,
+                       N->act(4), N->act_lo(4), N->w() + net_param_offset(5), y);
     return hipGetLastError();
 }
 

@@ -54,7 +54,12 @@ __global__ void k_finish(const float *groups, float *grad, const double *lpart, 
                          float *m, float *v, __bf16 *w16, __bf16 *w16lo, __bf16 *wt16, float lr, float b1, float b2,
                          float eps, float c1, float c2);
 __global__ void k_conv_in(const float *x, const float *w1, __bf16 *out, __bf16 *out_lo, int per, int dil);
+template <int OUT>
 __global__ void k_conv_out(const __bf16 *in, const __bf16 *in_lo, const float *w6, float *y);
+// Batches of at most this many images run k_conv_out<1>: one workgroup a class
+// leaves CUs idle there.  1, 2, 4, 8 and 16 images: 7.4, 7.7, 8.5, 9.4 and 14.8 us
+// so, 8.1, 8.7, 9.0, 10.2 and 12.4 with <2>.
+constexpr int kConvOutSplitMaxBatch = 8;
 __global__ void k_conv_out_bwd(const float *dy, const float *w6, __bf16 *g, int per, int dil);
 // Pixels per thread of k_conv_in and k_conv_out_bwd (workgroups of 64 x that
 // many): as many as leave four workgroups per CU (1024), at most 16.

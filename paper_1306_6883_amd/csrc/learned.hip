@@ -516,10 +516,12 @@ __global__ __launch_bounds__(256) void k_conv_in(const float *__restrict__ x, co
 // Last layer (32 -> 1): (hi + lo) activations, FP32 weights and output.  Rows
 // 32 apart need only each other (four rows, circular), so a workgroup reads
 // four of them once, as FP32 sums hi + lo in LDS, and makes their 512 outputs,
-// two per thread; the sum runs over tap, then channel.  A pixel's eight
+// OUT = 2 per thread, or half of them (OUT = 1, two workgroups to a class);
+// the sum runs over tap, then channel.  A pixel's eight
 // 16-byte chunks are swizzled (chunk c of pixel x at c ^ (x / 2) % 8: any 16
 // consecutive pixels' chunks lie in 16 different bank groups).
 // (64 images: 82 -> 37 us.)
+template <int OUT>
 __global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
                                                      const float *__restrict__ w6, float *__restrict__ y) {
     constexpr int D = 1 << (kNetLayers - 1);
@@ -527,7 +529,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ 
     __shared__ __attribute__((aligned(16))) float act[4][kNetG * kNetC];
     const int tid = threadIdx.x;
     const int blk = xcd_block();
-    const int b = blk / D, y0 = blk % D;
+    const int half = OUT == 1 ? blk & 1 : 0, cls = OUT == 1 ? blk >> 1 : blk;
+    const int b = cls / D, y0 = cls % D;
     auto place = [](int x, int c) { return x * kNetC + 4 * ((c ^ (x >> 1)) & 7); };
 #pragma unroll
     for (int row = 0; row < 4; ++row) {
@@ -553,8 +556,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ 
         }
     }
     __syncthreads();
-    const int x = tid & (kNetG - 1), r0 = tid >> 7;  // rows r0 and r0 + 2 of the class
-    float s[2] = {0.f, 0.f};
+    const int x = tid & (kNetG - 1), r0 = (tid >> 7) + 2 * half;  // row r0 of the class (and r0 + 2)
+    float s[OUT] = {};
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int xs = wrapg(x + tap_dx(t, D));
@@ -562,7 +565,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ 
         for (int c = 0; c < 8; ++c) {
             const int at = place(xs, c);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < OUT; ++k) {
                 const float4 v = *reinterpret_cast<const float4 *>(&act[(r0 + 2 * k + t / 3 + 3) & 3][at]);
                 const float *wt = w6 + t * kNetC + 4 * c;
                 s[k] += wt[0] * v.x;
@@ -573,8 +576,10 @@ __global__ __launch_bounds__(256, 2) void k_conv_out(const __bf16 *__restrict__ 
         }
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) y[((size_t)b * kNetG + y0 + D * (r0 + 2 * k)) * kNetG + x] = s[k];
+    for (int k = 0; k < OUT; ++k) y[((size_t)b * kNetG + y0 + D * (r0 + 2 * k)) * kNetG + x] = s[k];
 }
+template __global__ void k_conv_out<1>(const __bf16 *, const __bf16 *, const float *, float *);
+template __global__ void k_conv_out<2>(const __bf16 *, const __bf16 *, const float *, float *);
 
 // Input gradient of the last layer: g[b][p][ci] = sum_tap w6[tap][ci] * dy[b][p - off(tap)].
 // (32 images: 19 -> 16 us.)

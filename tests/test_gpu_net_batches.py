@@ -56,3 +56,13 @@ def test_gradients_match_oracle(nb):
         print(f"layer {l + 1}: {e:.2e}")
         assert e < 1e-3, l
         o += sz
+
+
+@pytest.mark.parametrize("nb", [3, 8])
+def test_last_layer_in_halves(nb):
+    """The last layer in two workgroups a class (up to 8 images) and in one
+    (from 9): the same sums in the same order."""
+    print(f"last layer, batch {nb}", flush=True)
+    net, p = make(9, seed=5)
+    x = images(9, 11)
+    assert torch.equal(cc.ccmg_net_forward(net, x[:nb].contiguous()), cc.ccmg_net_forward(net, x)[:nb])
