@@ -61,10 +61,11 @@ __device__ __forceinline__ int xcd_block() {
 // images): one 32-pixel tile of a row per workgroup of 192; wavefront s takes
 // taps 3s .. 3s + 2 straight from memory and the first adds the other two's
 // partial sums from LDS, (acc0 + acc1) + acc2.
-__global__ __launch_bounds__(192) void k_conv32_split(const __bf16 *__restrict__ in, const __bf16 *__restrict__ in_lo,
-                                                      const __bf16 *__restrict__ w, const __bf16 *__restrict__ w_lo,
-                                                      __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int nb,
-                                                      int dil) {
+__global__ __launch_bounds__(192, 3) void k_conv32_split(const __bf16 *__restrict__ in,
+                                                         const __bf16 *__restrict__ in_lo,
+                                                         const __bf16 *__restrict__ w,
+                                                         const __bf16 *__restrict__ w_lo, __bf16 *__restrict__ out,
+                                                         __bf16 *__restrict__ out_lo, int nb, int dil) {
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tileno = xcd_block();
@@ -77,6 +78,10 @@ __global__ __launch_bounds__(192) void k_conv32_split(const __bf16 *__restrict__
     const int r = lane & 31, hk = lane >> 5;
     const size_t img = (size_t)b * kNetG * kNetG * kNetC;
     f32x16 acc = {};
+    // every load before the first product: left to itself the compiler takes 48
+    // registers and a few loads at a time (one image 6.1 us a layer, two 9.2;
+    // so 5.7 and 8.4, with three waves per SIMD at two images either way)
+    bf16x8 av[3][2], al[3][2], bv[3][2], bl[3][2];
 #pragma unroll
     for (int tt = 0; tt < 3; ++tt) {
         const int t = 3 * wib + tt;
@@ -85,14 +90,22 @@ __global__ __launch_bounds__(192) void k_conv32_split(const __bf16 *__restrict__
         const size_t px = img + ((size_t)ys * kNetG + xs) * kNetC;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const size_t wo = ((size_t)r * 9 + t) * kNetC + 16 * h + 8 * hk;
-            const bf16x8 bv = load8(w + wo);
-            const bf16x8 av = load8(in + px + 16 * h + 8 * hk);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(in_lo + px + 16 * h + 8 * hk), bv, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, load8(w_lo + wo), acc, 0, 0, 0);
+            const int wo = (r * 9 + t) * kNetC + 16 * h + 8 * hk;
+            bv[tt][h] = load8(w + wo);
+            av[tt][h] = load8(in + px + 16 * h + 8 * hk);
+            al[tt][h] = load8(in_lo + px + 16 * h + 8 * hk);
+            bl[tt][h] = load8(w_lo + wo);
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int tt = 0; tt < 3; ++tt)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[tt][h], bv[tt][h], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[tt][h], bv[tt][h], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[tt][h], bl[tt][h], acc, 0, 0, 0);
+        }
     __shared__ float part[2][16][64];
     if (wib > 0)
 #pragma unroll
