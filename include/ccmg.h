@@ -448,13 +448,15 @@ int ccmg_solve_learned(ccmg_plan *plan, ccmg_net *net, const double *d_f, double
 int ccmg_plan_autotune(ccmg_plan *plan, const double *d_f, double *d_phi, ptrdiff_t pitch);
 /* Set one launch shape by hand: kind 0 = the nu1 (restricting) launch of
  * `level`, 1 = the nu2 (prolongating) launch; ty even, >= 8 unless it covers
- * the level; 1 <= wpb <= 4 (bands of 8 and 16 rows that are held in registers
- * whole run one wave per workgroup).  ty = 0 runs as ty = 8 (levels below the
+ * the level; 1 <= wpb <= 4.  ty = 0 runs as ty = 8 (levels below the
  * finest with at least 64 cells per side that are not in the one-workgroup
- * tail).  The 64 x 64 level runs in one launch with the tail wherever its
- * correction starts from zero (its shapes are then unused).  kind 2 = the fused finest launch of FP64 solves, 3 = its FP32 form in
- * mixed-precision steps (level 0 only, ty even and >= 8).  Levels below the finest that are not
- * in the tail, run as a visit (CCMG_OPT_VISIT): kind 4 = the restricting
+ * tail).  A 64 x 64 level below the finest runs in one launch with the tail
+ * wherever its correction starts from zero, as long as both its shapes are the
+ * default ones (ty = 8, wpb = 1, which ccmg_plan_autotune keeps) and it is not
+ * set to run as a visit; any other shape set here has it run its own launches.
+ * kind 2 = the fused finest launch of FP64 solves, 3 = its FP32 form in
+ * mixed-precision steps (level 0 only, ty even and >= 8).  Levels below the
+ * finest that are not in the tail, run as a visit (CCMG_OPT_VISIT): kind 4 = the restricting
  * launch without the stored iterate (as kind 0), kind 5 = the visit launch
  * (row march only, ty even and >= 16 unless it covers the level; ty = 0 sets
  * the level to run its two launches instead, and with CCMG_OPT_VISIT = 1

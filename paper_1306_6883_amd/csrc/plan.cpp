@@ -341,6 +341,13 @@ bool visit_level(const ccmg_plan *P, int l) {
         return false;
     return P->opt_visit == 2 || P->visit[l];
 }
+// Level l is the 64 x 64 one, below the finest, whose launches the tail's can
+// take over: unless shapes other than the default were set for them by hand.
+bool joins_tail(const ccmg_plan *P, int l) {
+    auto plain = [](const MarchShape &s) { return s.ty == 8 && s.wpb == 1; };
+    return l >= 1 && l == P->lay.lt - 1 && P->lay.lev[l].n == 2 * kCoarseMax && plain(P->shp_pre[l]) &&
+           plain(P->shp_post[l]);
+}
 
 }  // namespace
 
@@ -536,8 +543,7 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
     // the level above the tail (64 x 64), where its correction starts from
     // zero, runs in one launch with it
     const int l64 = lay.lt - 1;
-    const bool with64 = lay.lt >= 2 && lay.lev[lay.lt].n == kCoarseMax && l64 >= 1 &&
-                        (io.coarse_only || l64 > top) && !(visits_ok && P->opt_visit == 2);
+    const bool with64 = joins_tail(P, l64) && (io.coarse_only || l64 > top) && !(visits_ok && visit_level(P, l64));
     const int ltail = with64 ? l64 : lay.lt;
     // down
     if (io.coarse_only) fpart_count[1] = io.f1_count;
@@ -1255,6 +1261,11 @@ hipError_t autotune_levels(ccmg_plan *P, const double *d_f, double *d_phi, ptrdi
     for (int l = 0; l < lay.lt && err == hipSuccess; ++l) {
         const int n = lay.lev[l].n, reps = reps_for(n), warm = warm_for(n);
         int sums_next = 0;
+        if (l >= 1 && l == lay.lt - 1 && n == 2 * kCoarseMax && l < kMaxLevels) {  // one launch with the tail
+            P->shp_pre[l] = P->shp_pre_v[l] = P->shp_post[l] = level_shape_for(n, P->singular, true);
+            P->visit[l] = false;
+            break;  // (the last of these levels)
+        }
         // kinds 0 / 1: the level's restricting and prolongating launches;
         // 2 / 3: the same level as a visit (restricting launch without the
         // stored iterate, visit launch), on levels where a visit applies and
