@@ -76,3 +76,27 @@ def test_ends_without_a_cycle(n):
     with pytest.raises(cc.CcmgError) as e:
         solve(n, "DDDD", (0.0, -1.0), fv, g, False)
     assert e.value.status == cc.ENONFINITE
+
+
+@pytest.mark.parametrize("nu", [(0, 2), (1, 1), (2, 0), (3, 1)])
+@pytest.mark.parametrize("bc,ab", [("DNND", (0.0, -1.0)), ("PPDN", (1.0, 2e-4)), ("PPPP", (0.0, -1.0))])
+@pytest.mark.parametrize("n", [32, 64])
+def test_other_smoothing_counts(n, bc, ab, nu):
+    """The same comparison for smoothing counts other than two, no sweep on
+    one side among them (nobody but the start then publishes the 64 x 64
+    level's edges), over five cycles from zero and from a guess."""
+    print(f"solo n={n} bc={bc} ab={ab} nu={nu}", flush=True)
+    fv = np.random.default_rng(52).standard_normal((n, n))
+    fv -= fv.mean()
+    singular = ab[0] == 0.0 and "D" not in bc
+    kw = dict(nu1=nu[0], nu2=nu[1], max_cycles=5, rtol=0.0)
+    for guess in (None, W.fourier_modes(n, seed=4, count=8, kmax=4) * 1e-3):
+        r, phi = solve(n, bc, ab, fv, guess, False, **kw)
+        s, ref = solve(n, bc, ab, fv, guess, True, **kw)
+        assert r.status == s.status == cc.NOT_CONVERGED and r.cycles == s.cycles == 5
+        h, hr = np.array(r.history), np.array(s.history)
+        np.testing.assert_allclose(h[hr > 1e-9], hr[hr > 1e-9], rtol=1e-9 if not singular else 1e-6)
+        if singular:
+            assert np.abs(phi - ref).max() <= 1e-12 * np.abs(ref).max()
+        else:
+            assert np.array_equal(phi, ref)
