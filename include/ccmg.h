@@ -211,7 +211,7 @@ int ccmg_plan_get_option(ccmg_plan *plan, int option, double *value);
  * A + c 1 1^T, c = beta / h^2, whose solution of a zero-mean f is the
  * zero-mean solution), and the levels below it are not visited; nu_bottom is
  * then unused.  A^-1 is computed here on the device (Gauss-Jordan in FP64,
- * n_bottom^4 doubles in the plan's workspace) and applied in FP64 from LDS by
+ * n_bottom^4 doubles in the plan's workspace) and applied in FP64 by
  * the one-workgroup tail, also in the FP32 cycles of mixed plans.  Applies to
  * every later ccmg_solve, ccmg_vcycle, ccmg_solve_bc, ccmg_cn_step and
  * ccmg_project of the plan.  Returns CCMG_EINVAL for another size, a size

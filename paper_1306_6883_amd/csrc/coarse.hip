@@ -11,7 +11,7 @@
 // recursion, centred-slope prolongation without the xy term, nu2 iterations;
 // on the 2 x 2 grid nu_bottom relaxations, done in FP64 whatever T is.  Or an
 // exact bottom on a 4 x 4 or 8 x 8 level: its inverse operator (computed once
-// per plan by k_bottom_inverse) is held in LDS and applied in FP64.
+// per plan by k_bottom_inverse) is applied in FP64.
 #include <cstdlib>
 
 #include "internal.h"
@@ -23,8 +23,9 @@ namespace {
 // Workgroup size NT of coarse_body (a template parameter).  With NT = 64 (one
 // wavefront: a batch's small grids) no workgroup barrier is needed -- a wave's
 // LDS operations complete in issue order, so ordering the compiler's code is
-// enough between phases.
+// enough between phases.  Largest level it holds; a larger tail is tail_body's.
 constexpr int kCoarseThreads = 512;
+constexpr int kBodyMax = kCoarseMax / 2;
 
 template <int NT>
 __device__ __forceinline__ void sync() {
@@ -261,8 +262,8 @@ __device__ void direct_bottom(const double *sInv, T *P, const T *F, int lg) {
 
 template <int NT, typename T, bool DIRECT>
 __device__ void coarse_body(const CoarseArgs<T> &a) {
-    __shared__ T sP[kCoarseMax * kCoarseMax * 4 / 3 + 8];
-    __shared__ T sF[kCoarseMax * kCoarseMax * 4 / 3 + 8];
+    __shared__ T sP[kBodyMax * kBodyMax * 4 / 3 + 8];
+    __shared__ T sF[kBodyMax * kBodyMax * 4 / 3 + 8];
     __shared__ double red[NT / 64];
     __shared__ double sInv[DIRECT ? kDirectMax * kDirectMax * kDirectMax * kDirectMax : 1];
     if (a.skip && *a.skip) return;  // uniform over the workgroup

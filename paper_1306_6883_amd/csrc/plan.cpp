@@ -630,7 +630,7 @@ hipError_t enqueue_cycle(ccmg_plan *P, const CycleIO<T> &io, int *norm_tiles) {
         c.load_phi = (l == top && !io.coarse_only && !io.zero) ? 1 : 0;
         c.phi_in = cur[l].p;
         c.pin = cur[l].pitch;
-        c.phi_out = cur[l].p;  // the tail reads everything into LDS first
+        c.phi_out = cur[l].p;  // the tail reads the whole level before it writes
         c.pout = cur[l].pitch;
         c.phi_shift = (l == 0) ? io.phi_shift : nullptr;
         c.skip = io.skip;
