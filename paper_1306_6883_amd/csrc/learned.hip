@@ -141,7 +141,9 @@ __global__ __launch_bounds__(192, 3) void k_conv32_split(const __bf16 *__restric
 // PAIR: activations and weights are (hi, lo) pairs; else single BF16.
 // Walks of `seg` rows: workgroup = (image, row class y % dil, segment).
 // Measured, 64 images in pairs: 206 -> 64 us a layer (4.2 TB/s of the 268 MB it
-// reads and writes, 0.9 PFLOP/s of MFMAs); a training step of 32 images, whose
+// reads and writes, 0.9 PFLOP/s of MFMAs: busy a third of the launch, the LDS a
+// seventh; half of the waves' time goes waiting to issue, an output row being 54
+// dependent MFMAs on one accumulator, two waves to a SIMD); a training step of 32 images, whose
 // eight launches averaged 67.5 us: 36 us forward, 16 us for a gradient.
 namespace {
 constexpr int kRowBytes = kNetG * kNetC * 2;  // one row of one plane: 8 KB
